@@ -90,14 +90,6 @@ struct GemmShape {
 // (r & 7) ^ (r >> 3 & 1), which conflicted in the 32-lane groups.
 __device__ __forceinline__ int chunk_swz(int r) { return ((r >> 1) & 3) | (((r ^ (r >> 3)) & 1) << 2); }
 
-// s_waitcnt lgkmcnt(N) alone (vmcnt and expcnt left at their maxima).
-template <int N>
-__device__ __forceinline__ void wait_lds_but() {
-  static_assert(N >= 0 && N < 16, "lgkmcnt range");
-  __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
-}
-__device__ __forceinline__ void wait_lds() { wait_lds_but<0>(); }
-
 // True when each of h groups of m products (split as evenly as integer
 // division gives) has a product ahead of each of its accesses: a store, a
 // load and its share of f fragment reads.

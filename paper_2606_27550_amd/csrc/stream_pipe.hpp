@@ -22,12 +22,32 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (0 << 8));
 }
 
+// s_waitcnt lgkmcnt(N) alone (vmcnt and expcnt left at their maxima).
+template <int N>
+__device__ __forceinline__ void wait_lds_but() {
+  static_assert(N >= 0 && N < 16, "lgkmcnt range");
+  __builtin_amdgcn_s_waitcnt(0xC07F | (N << 8));
+}
+__device__ __forceinline__ void wait_lds() { wait_lds_but<0>(); }
+
 // One direct global->LDS copy of 16 bytes per lane: lane l's bytes land at
 // lds + 16 * l (lds is wave-uniform).  Kept in a device-only function: in a
 // kernel's (host+device) lambda this gfx950 builtin would keep the compiler
 // from emitting the kernel's host launch stub.
 __device__ __forceinline__ void lds_dma16(const void* src, void* lds) {
   __builtin_amdgcn_global_load_lds(src, lds, 16, 0, 0);
+}
+
+// The same copy through a buffer descriptor (lane l from byte voff(l) of the
+// buffer; bytes past its end arrive as zeros).  global_load_lds counts as a flat access, beside which the
+// compiler makes every wait for an ordinary load a full drain; beside buffer
+// copies its counted waits stay exact, and the address is one 32-bit offset.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t dma_buffer(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ void buf_dma16(__amdgpu_buffer_rsrc_t buf, uint32_t voff, void* lds) {
+  typedef __attribute__((address_space(3))) void lds_void;
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (lds_void*)lds, 16, voff, 0, 0, 0);
 }
 
 // Workgroup barrier without a memory-model fence.  __syncthreads() would add

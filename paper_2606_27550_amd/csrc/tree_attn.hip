@@ -20,12 +20,13 @@
 //     current one (K two blocks deep in registers, V one); the tile's
 //     fragments live once per workgroup in LDS, and the four waves merge in
 //     LDS at the end.  Larger trees: a workgroup owns four tiles, one per
-//     wave, and the waves walk the same key blocks, staged once per
-//     workgroup in LDS (K as rows, V transposed), so a block is read once per
+//     wave, and the waves walk the same key blocks, copied once per
+//     workgroup straight into a ring in LDS, so a block is read once per
 //     128 rows; that kernel stays under 256 registers per lane, two
 //     workgroups per CU.
 //     S^T = K Q^T and O^T += V^T P^T run on v_mfma_f32_32x32x16_bf16, V
-//     transposed through LDS, P never leaving registers (the S^T accumulator
+//     transposed through LDS (by the LDS read itself in the four-tile
+//     kernel), P never leaving registers (the S^T accumulator
 //     layout is re-read as the B operand of the PV product after a fixed key
 //     permutation).  Blocks wholly inside the prefix skip the mask; the
 //     others take a 32-bit window cut from the node's ancestor bitmask.
@@ -39,8 +40,10 @@
 #include <cfloat>
 #include <cmath>
 #include <mutex>
+#include <type_traits>
 
 #include "common.hpp"
+#include "stream_pipe.hpp"
 
 namespace entmtp {
 namespace {
@@ -169,12 +172,15 @@ struct BatchArgs {
 static_assert(sizeof(BatchArgs) <= 4096, "kernel arguments are limited to 4 KB");
 
 // Sequence that owns index `x` of a grid whose per-sequence ranges start at
-// `first(b)` (uniform per workgroup; at most kMaxSeqs steps).
+// `first(b)`, in increasing order (uniform per workgroup): lane i compares
+// with sequence i's start, so a batch costs one memory round trip however
+// many sequences it has.  Called by whole wavefronts.
 template <typename F>
 __device__ __forceinline__ int seq_of(const BatchArgs& p, int x, F first) {
-  int b = 0;
-  while (b + 1 < p.B && x >= first(p.s[b + 1])) ++b;
-  return b;
+  if (p.B == 1) return 0;
+  const int lane = threadIdx.x & 63;
+  const bool owns = lane < p.B && x >= first(p.s[lane < p.B ? lane : 0]);
+  return __popcll(__ballot(owns)) - 1;
 }
 
 // Plan of sequence b: the host's, or -- for a device-planned call -- the
@@ -300,26 +306,56 @@ constexpr int kRopePairs = HD / 2;
 inline size_t rope_lds_bytes(int D, double theta) {
   return theta > 0.0 ? static_cast<size_t>(D + 1) * kRopePairs * (sizeof(double2) + sizeof(float2)) : 0;
 }
-__device__ __forceinline__ const float2* rope_table_f32(const double2* tab, int D) {
-  return reinterpret_cast<const float2*>(tab + (D + 1) * kRopePairs);
+__device__ __forceinline__ float2* rope_table_f32(double2* tab, int D) {
+  return reinterpret_cast<float2*>(tab + (D + 1) * kRopePairs);
 }
 inline void set_rope(BatchArgs& a, float rope_theta) {
   a.theta = static_cast<double>(rope_theta);
   for (int c = 0; c < kRopePairs; ++c) a.freq[c] = a.theta > 0.0 ? std::pow(a.theta, -2.0 * c / HD) : 0.0;
 }
-// f: this thread's pair frequency, freq[threadIdx.x % 64], loaded by the
-// caller ahead of its bulk loads (a load issued behind them would wait for
-// them).
-__device__ __forceinline__ void rope_table(double2* tab, int D, int L, double f) {
+// sin and cos of x in fp64, 0 <= x < 2^31 (positions times frequencies up to
+// one radian): x less the nearest multiple n of pi/2 (pi/2 as a sum of two
+// doubles, each product exact in its fused multiply-add: the remainder is
+// off by a rounding of its own size), then the Taylor series on [-pi/4,
+// pi/4], cut where the next term is below 1e-17 of the value.  About 40 fp64
+// instructions; the library's sincos, made for all arguments, took most of
+// the attention kernels' prologue.
+__device__ __forceinline__ double2 cos_sin(double x) {
+  const double n = rint(x * 0.63661977236758134308);   // 2 / pi
+  const double r = fma(-n, 6.123233995736766035869e-17, fma(-n, 1.57079632679489655800, x));
+  const double z = r * r;
+  double s = 1.0 / 355687428096000.0;                  // 1 / 17!
+  s = fma(s, z, -1.0 / 1307674368000.0);
+  s = fma(s, z, 1.0 / 6227020800.0);
+  s = fma(s, z, -1.0 / 39916800.0);
+  s = fma(s, z, 1.0 / 362880.0);
+  s = fma(s, z, -1.0 / 5040.0);
+  s = fma(s, z, 1.0 / 120.0);
+  s = fma(s, z, -1.0 / 6.0);
+  s = fma(s * z, r, r);
+  double c = 1.0 / 20922789888000.0;                   // 1 / 16!
+  c = fma(c, z, -1.0 / 87178291200.0);
+  c = fma(c, z, 1.0 / 479001600.0);
+  c = fma(c, z, -1.0 / 3628800.0);
+  c = fma(c, z, 1.0 / 40320.0);
+  c = fma(c, z, -1.0 / 720.0);
+  c = fma(c, z, 1.0 / 24.0);
+  c = fma(c, z, -0.5);
+  c = fma(c, z, 1.0);
+  const int q = static_cast<int>(n) & 3;   // quarter turns
+  const double a = q & 1 ? s : c, b = q & 1 ? c : s;
+  return make_double2(q == 1 || q == 2 ? -a : a, q >= 2 ? -b : b);
+}
+
+// Calls put(d, c, (cos, sin)) for the angles of positions L + d, d = 0..D,
+// over the workgroup.  f: this thread's pair frequency, freq[threadIdx.x %
+// 64], loaded by the caller ahead of its bulk loads (a load issued behind
+// them would wait for them).
+template <typename F>
+__device__ __forceinline__ void rope_table(int D, int L, double f, F put) {
   const int c = threadIdx.x % kRopePairs;
-  for (int d = threadIdx.x / kRopePairs; d <= D; d += blockDim.x / kRopePairs) {
-    const double pos = static_cast<double>(L) + static_cast<double>(d);
-    double sn, cs;
-    sincos(pos * f, &sn, &cs);
-    tab[d * kRopePairs + c] = make_double2(cs, sn);
-    reinterpret_cast<float2*>(tab + (D + 1) * kRopePairs)[d * kRopePairs + c] =
-        make_float2(static_cast<float>(cs), static_cast<float>(sn));
-  }
+  for (int d = threadIdx.x / kRopePairs; d <= D; d += kAttnThreads / kRopePairs)
+    put(d, c, cos_sin((static_cast<double>(L) + static_cast<double>(d)) * f));
 }
 
 // Turns the 8 pairs (c0 + e, c0 + e + 64), e < 8, whose halves lo / hi hold
@@ -533,9 +569,13 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attn_kernel(BatchArgs p) {
   s_mask[tid / ENTMTP_MASK_WORDS][tid % ENTMTP_MASK_WORDS] = mrow < GT ? mword : 0xFFFFFFFFu;
   const bool rope = p.theta > 0.0;
   if (rope) {
-    rope_table(s_rope, sq.D, L, freq);
+    float2* const tab32 = rope_table_f32(s_rope, sq.D);
+    rope_table(sq.D, L, freq, [&](int d, int pr, double2 cs) {
+      s_rope[d * kRopePairs + pr] = cs;
+      tab32[d * kRopePairs + pr] = make_float2(static_cast<float>(cs.x), static_cast<float>(cs.y));
+    });
     __syncthreads();
-    if (qlive) rope_pairs_f32(qlo, qhi, rope_table_f32(s_rope, sq.D) + qdepth * kRopePairs + 16 * qs + 8 * qhl);
+    if (qlive) rope_pairs_f32(qlo, qhi, tab32 + qdepth * kRopePairs + 16 * qs + 8 * qhl);
   }
   s_qf[0][qs][lane] = qlive ? qlo : u32x4{0u, 0u, 0u, 0u};
   s_qf[0][qs + 4][lane] = qlive ? qhi : u32x4{0u, 0u, 0u, 0u};
@@ -828,13 +868,43 @@ __global__ __launch_bounds__(kAttnThreads) void tree_attn_kernel(BatchArgs p) {
 }
 
 // Four query tiles per workgroup, one per wave (trees with more than 32
-// query rows per KV head; waves past the tree's last tile only load): the four waves walk the same key blocks, which
-// the workgroup stages once in LDS -- K as rows, V transposed -- from
-// coalesced loads (16 lanes per 256-byte key row), double-buffered with one
-// barrier per block and two blocks in flight in registers, so a KV block is
-// read once per 128 query rows.  Each wave keeps its own tile's Q fragments,
-// softmax state and output, so no cross-wave merge is needed.
-constexpr int KROW = HD + 8;   // bf16 per staged K row (16-byte pad: rows 4 banks apart)
+// query rows per KV head; waves past the tree's last tile only load).  The
+// four waves walk the same key blocks, which reach LDS by direct global->LDS
+// copies (no registers, no LDS stores) into a ring of kRing slots, one
+// barrier per block; K and V lie there as 256-byte rows, their 16-byte chunks
+// XOR-swizzled by row through the copies' source addresses.  The K Q^T
+// product reads K rows as they lie; the V^T operand of the P V product comes
+// from the transposing LDS read (ds_read_b64_tr_b16), four keys of one dim a
+// lane.  A KV block is then read once per 128 query rows, no cross-wave merge
+// is needed, and two workgroups share a CU.
+constexpr int kRing = 4;
+constexpr int kRingK = KB * HD * 2;          // bytes of a slot's K rows (V follows)
+constexpr int kRingSlot = 2 * kRingK;        // 16 KB
+constexpr int kRingLoads = kRingSlot / 16 / kAttnThreads;   // copies per thread and block
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// Four 16-bit elements of one column of a 4 x 16 block, the 16 lanes of a
+// group holding the block's columns: lane j of the group passes the address
+// of elements 4 (j % 4) .. + 3 of row j / 4 and receives column j.  (In a
+// device-only function, as lds_dma16.)
+__device__ __forceinline__ uint2 lds_read_tr(const uint8_t* p) {
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p));
+}
+
+// The larger of a lane's value and that of the lane 32 away.
+__device__ __forceinline__ float max_halves(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// Chunk c (16 bytes) of row r of a slot lies at chunk position c ^ k_swz(r)
+// (K) or c ^ v_swz(r) (V): a K fragment read takes one chunk of 16 rows, a
+// transposing read 32 lanes' 64 bytes of four rows; both then cover all banks.
+__device__ __forceinline__ int k_swz(int r) { return r & 15; }
+__device__ __forceinline__ int v_swz(int r) { return 4 * (r & 3); }
 
 template <bool DEVB>
 __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs p) {
@@ -854,18 +924,20 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
   const int GT = p.G * T;
   const int qt = qg * 4 + wave;           // this wave's query tile
   const bool live = qt < sq.nqt;          // (uniform per wave)
-  constexpr int QR = 4 * kQTile;
 
-  __shared__ __attribute__((aligned(16))) uint16_t s_k[2][KB][KROW];
-  __shared__ __attribute__((aligned(16))) uint32_t s_vt[2][HD * (VT_LD / 2)];
-  __shared__ uint32_t s_mask[QR][ENTMTP_MASK_WORDS + 1];
-  extern __shared__ __attribute__((aligned(16))) double2 s_rope[];   // angles of the tree's positions
+  // one LDS object per slot, so that the compiler can tell the slot being
+  // read from the slots the copies in flight write to
+  __shared__ __attribute__((aligned(16))) uint8_t slot0[kRingSlot];
+  __shared__ __attribute__((aligned(16))) uint8_t slot1[kRingSlot];
+  __shared__ __attribute__((aligned(16))) uint8_t slot2[kRingSlot];
+  __shared__ __attribute__((aligned(16))) uint8_t slot3[kRingSlot];
+  __shared__ uint8_t s_depth[ENTMTP_T_MAX];
+  uint8_t* const ring[4] = {slot0, slot1, slot2, slot3};
+  static_assert(kRing == 4, "the ring's slots");
 
   const size_t head_off = static_cast<size_t>(g) * p.cap * HD;
   uint16_t* const kc_head = sq.kc + head_off;
   uint16_t* const vc_head = sq.vc + head_off;
-  const uint16_t* kbase = kc_head;
-  const uint16_t* vbase = vc_head;
   const float c = p.scale_log2;
   const int nblocks = (nkeys + KB - 1) / KB;
   const int blk_lo = split * sq.bps;
@@ -876,76 +948,87 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
   // values in the cache (slots L .. L + T - 1) for the steps after this one
   const bool keeper = qg == 0;
 
-  // prefix keys from the cache, the tree's keys and values from the inputs
-  auto krow = [&](int key) {
-    return key < L ? kbase + static_cast<size_t>(key) * HD
-                   : p.kt + (static_cast<size_t>(sq.row0 + key - L) * p.Hkv + g) * HD;
-  };
-  auto vrow = [&](int key) {
-    return key < L ? vbase + static_cast<size_t>(key) * HD
-                   : p.vt + (static_cast<size_t>(sq.row0 + key - L) * p.Hkv + g) * HD;
-  };
-  // cooperative loads of one block: K unit u = tid + 256 j -> key u / 16,
-  // 16-byte chunk u % 16; V unit tid -> key pair tid / 16, 8-dim chunk
-  // tid % 16 (both keys of the pair).  Keys past the end clamp to the last.
-  auto gload = [&](int i, u32x4 (&kr)[2], u32x4& va, u32x4& vb) {
-    const int kb = (blk_lo + min(i, nb - 1)) * KB;
-    const int last = nkeys - 1;
+  // the split's first np blocks lie wholly in the prefix
+  const int np = max(0, min(nb, L / KB - blk_lo));
+
+  // copies of prefix block i (past the last: that one again) into a slot:
+  // instruction j of wave w fills rows 8 w + 4 j .. + 3 of K and of V, lane l
+  // the chunk position l % 16 of row l / 16 among them.  The buffers span the
+  // block; without a prefix block they are empty and the copies bring zeros
+  // that nothing reads, so that every path carries the same count.
+  const uint32_t blk_bytes = np > 0 ? kRingK : 0;
+  uint32_t koff[kRingLoads / 2], voffs[kRingLoads / 2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int u = tid + kAttnThreads * j;
-      const int key = min(kb + (u >> 4), last);
-      kr[j] = *reinterpret_cast<const u32x4*>(krow(key) + 8 * (u & 15));
-    }
-    const int m = tid & 15, pp = tid >> 4;
-    const int k0 = min(kb + 2 * pp, last), k1 = min(kb + 2 * pp + 1, last);
-    va = *reinterpret_cast<const u32x4*>(vrow(k0) + 8 * m);
-    vb = *reinterpret_cast<const u32x4*>(vrow(k1) + 8 * m);
-  };
-  // block i's registers into LDS buffer buf; a block that holds tree keys
-  // rotates them first (the pair's other half sits in lane ^ 8) and the
-  // keeper writes them and their values to the cache
-  auto stage = [&](int buf, int i, u32x4 (&kr)[2], const u32x4& va, const u32x4& vb) {
-    const int kb = (blk_lo + min(i, nb - 1)) * KB;
-    if (kb + KB > L) {
+  for (int j = 0; j < kRingLoads / 2; ++j) {
+    const int r = 4 * (wave * (kRingLoads / 2) + j) + (lane >> 4);
+    koff[j] = r * 256 + (((lane & 15) ^ k_swz(r)) << 4);
+    voffs[j] = r * 256 + (((lane & 15) ^ v_swz(r)) << 4);
+  }
+  auto gload = [&](uint8_t* slot, int i) {
+    const size_t off = static_cast<size_t>(blk_lo + min(i, max(np - 1, 0))) * (KB * HD);   // (uniform)
+    const __amdgpu_buffer_rsrc_t kbuf = dma_buffer(kc_head + off, blk_bytes);
+    const __amdgpu_buffer_rsrc_t vbuf = dma_buffer(vc_head + off, blk_bytes);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int u = tid + kAttnThreads * j;
-        const int key = kb + (u >> 4);
-        const int kk = min(key, nkeys - 1);
-        if (rope)
-          kr[j] = rope_half(kr[j], u & 15, kk >= L, s_rope + sq.depth[max(kk - L, 0)] * kRopePairs);
-        if (keeper && key >= L && key < nkeys)
-          *reinterpret_cast<u32x4*>(kc_head + static_cast<size_t>(key) * HD +
-                                    8 * (u & 15)) = kr[j];
-      }
-      const int m = tid & 15, pp = tid >> 4;
-      const int k0 = kb + 2 * pp, k1 = k0 + 1;
-      if (keeper && k0 >= L && k0 < nkeys)
-        *reinterpret_cast<u32x4*>(vc_head + static_cast<size_t>(k0) * HD + 8 * m) = va;
-      if (keeper && k1 >= L && k1 < nkeys)
-        *reinterpret_cast<u32x4*>(vc_head + static_cast<size_t>(k1) * HD + 8 * m) = vb;
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int u = tid + kAttnThreads * j;
-      *reinterpret_cast<u32x4*>(&s_k[buf][u >> 4][8 * (u & 15)]) = kr[j];
-    }
-    const int m = tid & 15, pp = tid >> 4;
-    uint32_t* vt = s_vt[buf];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      vt[(8 * m + 2 * w) * (VT_LD / 2) + pp] = __builtin_amdgcn_perm(vb[w], va[w], 0x05040100u);
-      vt[(8 * m + 2 * w + 1) * (VT_LD / 2) + pp] = __builtin_amdgcn_perm(vb[w], va[w], 0x07060302u);
+    for (int j = 0; j < kRingLoads / 2; ++j) {
+      const int r0 = 4 * (wave * (kRingLoads / 2) + j);
+      buf_dma16(kbuf, koff[j], slot + r0 * 256);
+      buf_dma16(vbuf, voffs[j], slot + kRingK + r0 * 256);
     }
   };
 
+  // Blocks that hold tree keys go through registers instead: thread (row
+  // tid / 8, cc = tid % 8) takes chunks cc and cc + 8 of its key and value
+  // row (the two halves of pairs 8 cc .. 8 cc + 7), rotates a tree key, and
+  // the keeper writes it and its value to the cache.  (In the main loop an
+  // ordinary load or an LDS store would wait for every copy in flight.)
+  auto tab64 = [&](int d) {   // angles at depth d, 16 depths a slot
+    return reinterpret_cast<double2*>(d < 16 ? slot2 : slot3) + (d & 15) * kRopePairs;
+  };
+  static_assert(16 * kRopePairs * sizeof(double2) <= kRingSlot && ENTMTP_D_MAX < 32, "the angles fit in two slots");
+  struct TreeRegs {
+    u32x4 k0, k1, v0, v1;
+  };
+  const int trow = tid >> 3, tcc = tid & 7;
+  auto tree_load = [&](TreeRegs& t, int i) {
+    const int key = min((blk_lo + min(i, nb - 1)) * KB + trow, nkeys - 1);
+    const size_t pre = static_cast<size_t>(key) * HD;
+    const size_t own = (static_cast<size_t>(sq.row0 + key - L) * p.Hkv + g) * HD;
+    const uint16_t* kp = (key < L ? kc_head + pre : p.kt + own) + 8 * tcc;
+    const uint16_t* vp = (key < L ? vc_head + pre : p.vt + own) + 8 * tcc;
+    t.k0 = *reinterpret_cast<const u32x4*>(kp);
+    t.k1 = *reinterpret_cast<const u32x4*>(kp + HD / 2);
+    t.v0 = *reinterpret_cast<const u32x4*>(vp);
+    t.v1 = *reinterpret_cast<const u32x4*>(vp + HD / 2);
+  };
+  auto tree_stage = [&](uint8_t* slot, TreeRegs& t, int i) {
+    const int key = (blk_lo + i) * KB + trow;
+    if (key >= L && key < nkeys) {
+      if (rope) rope_pairs(t.k0, t.k1, tab64(s_depth[key - L]) + 8 * tcc);
+      if (keeper) {
+        uint16_t* kd = kc_head + static_cast<size_t>(key) * HD + 8 * tcc;
+        uint16_t* vd = vc_head + static_cast<size_t>(key) * HD + 8 * tcc;
+        *reinterpret_cast<u32x4*>(kd) = t.k0;
+        *reinterpret_cast<u32x4*>(kd + HD / 2) = t.k1;
+        *reinterpret_cast<u32x4*>(vd) = t.v0;
+        *reinterpret_cast<u32x4*>(vd + HD / 2) = t.v1;
+      }
+    }
+    uint8_t* const row = slot + trow * 256;
+    *reinterpret_cast<u32x4*>(row + ((tcc ^ k_swz(trow)) << 4)) = t.k0;
+    *reinterpret_cast<u32x4*>(row + (((tcc + 8) ^ k_swz(trow)) << 4)) = t.k1;
+    *reinterpret_cast<u32x4*>(row + kRingK + ((tcc ^ v_swz(trow)) << 4)) = t.v0;
+    *reinterpret_cast<u32x4*>(row + kRingK + (((tcc + 8) ^ v_swz(trow)) << 4)) = t.v1;
+  };
+
+  double freq = p.freq[tid % kRopePairs];
+  TreeRegs tregs;
+  if (nb > np) tree_load(tregs, np);
+
   // The small loads go first (this wave's Q fragments, its rows' depths and
-  // the group's masks, all unconditional: rows past the tree read row 0 and
-  // are never stored): requested after the first two K/V blocks they waited
-  // behind every workgroup's 32 KB burst (measured: a 6 us prologue).
-  // Query row r of KV head g is (head g * G + r / T, node r % T); chunks s
-  // and s + 4 hold the two halves of pairs 16s + 8lh + e.
+  // masks, all unconditional: rows past the tree read row 0 and are never
+  // stored): behind the key blocks they would wait for every workgroup's
+  // burst.  Query row r of KV head g is (head g * G + r / T, node r % T);
+  // chunks s and s + 4 hold the two halves of pairs 16s + 8lh + e.
   u32x4 qf[8];
   const int qrow = qt * kQTile + li;
   const bool qlive = qrow < GT;
@@ -957,42 +1040,32 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
     for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const u32x4*>(qp + 16 * s);
   }
   const int qdepth = sq.depth[qnode];
-  constexpr int kMaskPer = QR * ENTMTP_MASK_WORDS / kAttnThreads;
-  static_assert(kMaskPer * kAttnThreads == QR * ENTMTP_MASK_WORDS, "mask words fill the threads");
-  uint32_t mw[kMaskPer];
+  const int tdepth = sq.depth[min(tid, T - 1)];
+  u32x4 mlo = *reinterpret_cast<const u32x4*>(sq.mask + qnode * ENTMTP_MASK_WORDS);
+  u32x4 mhi = *reinterpret_cast<const u32x4*>(sq.mask + qnode * ENTMTP_MASK_WORDS + 4);
+  static_assert(ENTMTP_MASK_WORDS == 8, "a mask row is two 16-byte loads");
 #pragma unroll
-  for (int j = 0; j < kMaskPer; ++j) {
-    const int u = tid + kAttnThreads * j;
-    const int mrow = qg * QR + u / ENTMTP_MASK_WORDS;
-    mw[j] = sq.mask[(mrow < GT ? mrow % T : 0) * ENTMTP_MASK_WORDS + u % ENTMTP_MASK_WORDS];
-  }
-  const double freq = p.freq[tid % kRopePairs];
-
-  u32x4 kA[2], kB[2], vaA, vbA, vaB, vbB;
-  gload(0, kA, vaA, vbA);
-  gload(1, kB, vaB, vbB);
-
-  // ancestor masks of the group's rows (padding rows see every key), the
-  // angle table and this wave's rotated Q fragments, while the blocks arrive
-#pragma unroll
-  for (int j = 0; j < kMaskPer; ++j) {
-    const int u = tid + kAttnThreads * j;
-    const int r = u / ENTMTP_MASK_WORDS;
-    s_mask[r][u % ENTMTP_MASK_WORDS] = qg * QR + r < GT ? mw[j] : 0xFFFFFFFFu;
-  }
+  for (int k = 0; k < kRing - 1; ++k) gload(ring[k], k);
+  // the angles, while the blocks arrive: the queries' fp32 table lies in the
+  // last slot, free until the loop's first copies
+  asm volatile("" : "+v"(freq));   // (the compiler would sink its load below the copies)
+  float2* const tab32 = reinterpret_cast<float2*>(slot3);
+  static_assert((ENTMTP_D_MAX + 1) * kRopePairs * sizeof(float2) <= kRingSlot, "the angles fit in a slot");
+  if (rope) rope_table(sq.D, L, freq, [&](int d, int pr, double2 cs) {
+    tab32[d * kRopePairs + pr] = make_float2(static_cast<float>(cs.x), static_cast<float>(cs.y));
+  });
+  s_depth[tid] = static_cast<uint8_t>(tdepth);
+  static_assert(kAttnThreads >= ENTMTP_T_MAX, "one thread per node");
+  wait_lds();
+  stage_barrier();
+  if (!qlive) mlo = mhi = u32x4{~0u, ~0u, ~0u, ~0u};   // padding rows see every key
   if (rope) {
-    rope_table(s_rope, sq.D, L, freq);
-    __syncthreads();
-    if (qlive) {
-      const float2* tr = rope_table_f32(s_rope, sq.D) + qdepth * kRopePairs + 8 * lh;
+    const float2* tr = tab32 + qdepth * kRopePairs + 8 * lh;
 #pragma unroll
-      for (int s = 0; s < 4; ++s) rope_pairs_f32(qf[s], qf[s + 4], tr + 16 * s);
-    }
+    for (int s = 0; s < 4; ++s) rope_pairs_f32(qf[s], qf[s + 4], tr + 16 * s);
   }
-  stage(0, 0, kA, vaA, vbA);
-  gload(2, kA, vaA, vbA);
-  __syncthreads();
 
+  // l_run: the sum of this lane's half of the keys (the halves meet at the end)
   float m_run = -INFINITY, l_run = 0.f;
   f32x16 o[4];
 #pragma unroll
@@ -1000,35 +1073,47 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[ct][r] = 0.f;
 
-  // block i of the split from LDS buffer buf: this wave's scores, softmax
-  // (lazily raised max, as in tree_attn_kernel) and P V
-  auto compute = [&](int i, int buf) {
-    if (!live) return;
-    const int kb = (blk_lo + i) * KB;
-    const bool plain = kb + KB <= L;
-    f32x16 sacc;
+  // fragment addresses within a slot: K row li, chunk 2 s + lh; the
+  // transposing reads of V: row 4 lh + (lane % 16) / 4 of each 8 rows, dims
+  // 32 ct + 16 (li / 16) + 4 (lane % 4)
+  const int kx = lh ^ k_swz(li);
+  const int vrow = 4 * lh + ((lane & 15) >> 2);
+  const int vx = (2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ v_swz(vrow);
+  const int voff = kRingK + vrow * 256 + 8 * (lane & 1);
+
+  // S^T = K Q^T of the block in a slot
+  auto scores = [&](const uint8_t* slot, f32x16& sacc) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
-      const u32x4 kf = *reinterpret_cast<const u32x4*>(&s_k[buf][li][16 * s + 8 * lh]);
+      const u32x4 kf = *reinterpret_cast<const u32x4*>(slot + li * 256 + ((kx ^ (2 * s)) << 4));
       sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf), as_bf16x8(qf[s]), sacc, 0, 0, 0);
     }
+  };
+  // block i's softmax (lazily raised max, as in tree_attn_kernel) and
+  // O^T += V^T P^T from its slot; prefix: every key of the block is visible
+  auto attend = [&](int i, const uint8_t* slot, f32x16& sacc, auto prefix) {
     float bmax = -INFINITY;
-    if (plain) {
+    if constexpr (decltype(prefix)::value) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) bmax = fmaxf(bmax, sacc[r]);
     } else {
+      const int kb = (blk_lo + i) * KB;
       uint32_t win = 0xFFFFFFFFu;
       const int rel = kb - L;
-      const uint32_t* mrow = s_mask[wave * kQTile + li];
+      auto word = [&](int w) {   // (w is uniform)
+        uint32_t x = 0u;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x = w == k ? (k < 4 ? mlo[k & 3] : mhi[k & 3]) : x;
+        return x;
+      };
       if (rel < 0) {
         const int npre = -rel;
-        win = (0xFFFFFFFFu >> (32 - npre)) | (mrow[0] << npre);
+        win = (0xFFFFFFFFu >> (32 - npre)) | (mlo[0] << npre);
       } else {
         const int wi = rel >> 5, sh = rel & 31;
-        const uint32_t lo = mrow[wi];
-        const uint32_t hi = wi + 1 < ENTMTP_MASK_WORDS ? mrow[wi + 1] : 0u;
+        const uint32_t lo = word(wi), hi = word(wi + 1);
         win = sh ? (lo >> sh) | (hi << (32 - sh)) : lo;
       }
 #pragma unroll
@@ -1039,7 +1124,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
         bmax = fmaxf(bmax, sacc[r]);
       }
     }
-    bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
+    bmax = max_halves(bmax);
     const float mb = bmax * c;
     const bool need = mb > m_run + kLazyLog2;
     if (__any(need)) {
@@ -1060,7 +1145,6 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
       pr[r] = __builtin_amdgcn_exp2f(fmaf(sacc[r], c, mneg));
       rsum += pr[r];
     }
-    rsum += __shfl_xor(rsum, 32, 64);
     l_run += rsum;
     bf16x8 pf[2];
 #pragma unroll
@@ -1072,37 +1156,90 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
                                                (f32x2{pr[8 * u + 2 * e], pr[8 * u + 2 * e + 1]}), bf16x2));
       pf[u] = as_bf16x8(w);
     }
-    const uint32_t* vt = s_vt[buf];
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) {
-      const uint32_t* row = vt + (32 * ct + li) * (VT_LD / 2);
+      const uint8_t* vp = slot + voff + ((vx ^ (4 * ct)) << 4);
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
-        const uint2 x0 = *reinterpret_cast<const uint2*>(row + 8 * u + 2 * lh);
-        const uint2 x1 = *reinterpret_cast<const uint2*>(row + 8 * u + 4 + 2 * lh);
+        const uint2 x0 = lds_read_tr(vp + 16 * u * 256);
+        const uint2 x1 = lds_read_tr(vp + (16 * u + 8) * 256);
         const u32x4 w = {x0.x, x0.y, x1.x, x1.y};
         o[ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(w), pf[u], o[ct], 0, 0, 0);
       }
     }
   };
 
-  // block i computes from buffer i & 1 while block i + 1 is staged into the
-  // other buffer and block i + 3 streams into the freed registers
-  for (int i = 0;; i += 2) {
-    compute(i, 0);
-    if (i + 1 >= nb) break;
-    stage(1, i + 1, kB, vaB, vbB);
-    gload(i + 3, kB, vaB, vbB);
+  // The prefix's blocks.  Step i takes the scores of block i + 1 ahead of
+  // block i's softmax, so that a wave has products to issue beside its
+  // exponentials; blocks i + 2 and i + 3 are in flight, the latter's copies
+  // going into the slot block i - 1 left, behind the barrier every wave
+  // reaches after its products.  Copies past the last block fetch it again,
+  // so the count in flight is always the same.
+  f32x16 sa, sb;
+  wait_vmcnt<(kRing - 2) * kRingLoads>();
+  stage_barrier();
+  if (live) scores(ring[0], sa);
+  int i0 = 0;
+  for (; i0 + kRing <= np; i0 += kRing) {
+#pragma unroll
+    for (int k = 0; k < kRing; ++k) {
+      wait_vmcnt<(kRing - 3) * kRingLoads>();
+      stage_barrier();
+      gload(ring[(k + kRing - 1) % kRing], i0 + k + kRing - 1);
+      if (live) {
+        f32x16& cur = k & 1 ? sb : sa;
+        scores(ring[(k + 1) % kRing], k & 1 ? sa : sb);
+        attend(i0 + k, ring[k], cur, std::true_type{});
+      }
+    }
+  }
+  // the last np % kRing blocks are in flight (a loop left from within its
+  // round would make the compiler add full waits)
+  wait_vmcnt<0>();
+  stage_barrier();
+  if (live) {
+#pragma unroll
+    for (int k = 0; k < kRing - 1; ++k)
+      if (i0 + k < np) {
+        f32x16& cur = k & 1 ? sb : sa;
+        if (k + 1 < kRing - 1) scores(ring[k + 1], k & 1 ? sa : sb);
+        attend(i0 + k, ring[k], cur, std::true_type{});
+      }
+  }
+
+  // the blocks that hold tree keys: staged into two of the slots in turn, the
+  // next block's loads ahead of this one's products, the keys' fp64 angles in
+  // the other two
+  if (nb > np) {
     __syncthreads();
-    compute(i + 1, 1);
-    if (i + 2 >= nb) break;
-    stage(0, i + 2, kA, vaA, vbA);
-    gload(i + 4, kA, vaA, vbA);
-    __syncthreads();
+    if (rope) {
+      rope_table(sq.D, L, freq, [&](int d, int pr, double2 cs) { tab64(d)[pr] = cs; });
+      __syncthreads();
+    }
+    tree_stage(slot0, tregs, np);
+    for (int i = np;; i += 2) {
+      tree_load(tregs, i + 1);
+      __syncthreads();
+      if (live) {
+        scores(slot0, sa);
+        attend(i, slot0, sa, std::false_type{});
+      }
+      if (i + 1 >= nb) break;
+      tree_stage(slot1, tregs, i + 1);
+      tree_load(tregs, i + 2);
+      __syncthreads();
+      if (live) {
+        scores(slot1, sa);
+        attend(i + 1, slot1, sa, std::false_type{});
+      }
+      if (i + 2 >= nb) break;
+      tree_stage(slot0, tregs, i + 2);
+    }
   }
 
   // this wave's tile: the output (one split) or its partial
   if (!live) return;
+  l_run += __shfl_xor(l_run, 32, 64);
   const int row = qt * kQTile + li;
   if (row >= GT) return;
   if (nsplit == 1) {
@@ -1216,11 +1353,12 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(BatchArgs p) 
 
 size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// lds: bytes of the rotation table (rope_lds_bytes of the deepest tree)
+// lds: bytes of the one-tile kernel's rotation table (rope_lds_bytes of the
+// deepest tree)
 template <bool DEVB = false>
 void launch_attend(const BatchArgs& a, int items, size_t lds, hipStream_t s) {
   if (a.nt == 4)
-    hipLaunchKernelGGL(tree_attn_q4_kernel<DEVB>, dim3(items), dim3(kAttnThreads), lds, s, a);
+    hipLaunchKernelGGL(tree_attn_q4_kernel<DEVB>, dim3(items), dim3(kAttnThreads), 0, s, a);
   else
     hipLaunchKernelGGL(tree_attn_kernel<DEVB>, dim3(items), dim3(kAttnThreads), lds, s, a);
 }
