@@ -7,26 +7,23 @@
 // path; it sits at sequence position prefix_len + depth(i).
 //
 // Two kernels, both on the caller's stream:
-//  1. attend: flash-decoding over the cache, one of two kernels.  The
-//     queries and the tree's keys are rotated to their positions as they are
-//     loaded (fp64 angles from a per-workgroup LDS table over the tree's
-//     depths, one bf16 rounding); the tree's keys and values come from the
-//     step's inputs rather than the cache, and the workgroups of the first
-//     query group write them (keys rotated) into cache slots [L, L+T) for
-//     the steps after this one.
-//     Trees of up to 32 query rows per KV head: a workgroup owns one (KV
-//     head, 32-query tile, key split); its four waves take interleaved 32-key
-//     blocks, each wave loading its next block while it multiplies the
-//     current one (K two blocks deep in registers, V one); the tile's
-//     fragments live once per workgroup in LDS, and the four waves merge in
-//     LDS at the end.  Larger trees: a workgroup owns four tiles, one per
-//     wave, and the waves walk the same key blocks, copied once per
-//     workgroup straight into a ring in LDS, so a block is read once per
-//     128 rows; that kernel stays under 256 registers per lane, two
-//     workgroups per CU.
+//  1. attend: flash-decoding over the cache.  The queries and the tree's keys
+//     are rotated to their positions as they are loaded (fp64 angles from a
+//     per-workgroup LDS table over the tree's depths, one bf16 rounding); the
+//     tree's keys and values come from the step's inputs rather than the
+//     cache, and the workgroups of the first query group write them (keys
+//     rotated) into cache slots [L, L+T) for the steps after this one.
+//     A workgroup owns one (KV head, group of four 32-row query tiles, key
+//     split), a tile per wave, and the waves walk the same 32-key blocks,
+//     copied once per workgroup straight into a ring in LDS, so a block is
+//     read once per 128 rows.  Trees of one tile run the same kernel with
+//     three waves only loading: a block then costs one wave 0.55 us, and the
+//     form that split the keys over the waves instead (a wave's keys in
+//     registers, merged through LDS at the end) took 14.6 us and a merge of
+//     4.1 where this one, unsplit, takes 12.8 (27 nodes, prefix 256), and
+//     43.3 us a call against 40.3 at prefix 8192 with 40 heads.
 //     S^T = K Q^T and O^T += V^T P^T run on v_mfma_f32_32x32x16_bf16, V
-//     transposed through LDS (by the LDS read itself in the four-tile
-//     kernel), P never leaving registers (the S^T accumulator
+//     transposed by the LDS read, P never leaving registers (the S^T accumulator
 //     layout is re-read as the B operand of the PV product after a fixed key
 //     permutation).  Blocks wholly inside the prefix skip the mask; the
 //     others take a 32-bit window cut from the node's ancestor bitmask.
@@ -37,6 +34,7 @@
 //     output normalised by its sum, in bf16 (half the bytes of fp32; a
 //     normalised partial stays within the range of the values).
 //     Skipped when a single split covers the keys.
+#include <algorithm>
 #include <cfloat>
 #include <cmath>
 #include <mutex>
@@ -57,60 +55,110 @@ constexpr int kAttnWaves = 4;
 constexpr int KB = 32;               // keys per block
 constexpr int kQTile = 32;           // query rows per tile
 constexpr float kLazyLog2 = 8.f;     // the running max is raised only past this many doublings
-constexpr int VT_LD = 36;            // bf16 per V^T row in LDS (32 keys + pad)
 constexpr int kMaxSplits = 32;
-constexpr int kMinBlocksPerSplit = 4;   // one block per wave at least
-// A batch's blocks-per-split target: its key-block streams (one per KV head,
-// query group and 32-key block: what a workgroup reads) over this many
-// workgroups per CU.
-constexpr int kBatchWgPerCu = 3;
+constexpr int kMinBlocksPerSplit = 4;
+// Sequences of up to this many key blocks are not split: a merge costs about
+// as much as ten blocks of one wave's products (launch, partials, its gap).
+// 27 nodes at prefixes 512 and 600: 24.0 us split, 19.2 and 19.8 unsplit; at
+// 700 (split either way) 24.
+constexpr int kLoneBlocks = 20;
+constexpr int kTilesPerWg = 4;       // query tiles per workgroup, one per wave
+constexpr int kWgPerCu = 2;          // attend workgroups resident per CU (registers, LDS)
 constexpr int kMaxSeqs = ENTMTP_B_MAX;
 
 __host__ __device__ inline int rows_padded(int G, int T) {
   return (G * T + kQTile - 1) / kQTile * kQTile;
 }
 
-// Workgroups along the query rows: groups of nt 32-row tiles.
-__host__ __device__ inline int query_groups(int nqt, int nt) { return (nqt + nt - 1) / nt; }
-
-// Query tiles per workgroup for a tree: one up to one tile of rows per KV
-// head, four (one per wave) above.  (The two-tile form -- both tiles in every
-// wave -- measured slower than four tiles with two waves idle: 23.5 against
-// 19.8 us at 64 rows and prefix 4096.)
-__host__ __device__ inline int tree_tiles(int G, int T) { return G * T > kQTile ? 4 : 1; }
+// Workgroups along the query rows: groups of four 32-row tiles.
+__host__ __device__ inline int query_groups(int nqt) { return (nqt + kTilesPerWg - 1) / kTilesPerWg; }
 
 __host__ __device__ inline int split_bound(int nblocks) {
-  int b = nblocks / kMinBlocksPerSplit;
-  b = b < 1 ? 1 : b;
+  if (nblocks <= kLoneBlocks) return 1;
+  const int b = nblocks / kMinBlocksPerSplit;
   return b > kMaxSplits ? kMaxSplits : b;
 }
 
-// Split count of a lone sequence: one workgroup fits per CU, so pick the
-// count that fills the CUs in whole rounds -- the first (1..bound) whose last
+// Split count of a lone sequence: pick the count that fills the resident
+// workgroups (slots) in whole rounds -- the first (1..bound) whose last
 // round is at least 90% full, else the fullest one seen (integer arithmetic,
 // so that the host and the device choose alike).
-__host__ __device__ inline int split_for_bound(int bound, int base_wg, int cus) {
+__host__ __device__ inline int split_for_bound(int bound, int base_wg, int slots) {
   int best = 1;
   long long best_wg = 0, best_rounds = 1;
   for (int ns = 1; ns <= bound; ++ns) {
     const long long wg = static_cast<long long>(base_wg) * ns;
-    const long long rounds = (wg + cus - 1) / cus;
+    const long long rounds = (wg + slots - 1) / slots;
     if (wg * best_rounds > best_wg * rounds) {   // fill wg / (rounds * cus) improves
       best_wg = wg;
       best_rounds = rounds;
       best = ns;
     }
-    if (10 * wg >= 9 * rounds * cus) break;
+    if (10 * wg >= 9 * rounds * slots) break;
   }
   return best;
 }
 
-// Workgroups of an instance resident per CU: two for the four-tile kernel
-// (under 256 registers per lane), one for the others.
-__host__ __device__ inline int wg_per_cu(int nt) { return nt == 4 ? 2 : 1; }
-
 __host__ __device__ inline int split_single(int nblocks, int base_wg, int cus) {
-  return split_for_bound(split_bound(nblocks), base_wg, cus);
+  return split_for_bound(split_bound(nblocks), base_wg, cus * kWgPerCu);
+}
+
+// Where split k of ns begins: even shares of nblocks + tree_extra blocks, the
+// last split, which holds the tree's keys, shorter by tree_extra.  A block of
+// tree keys is rotated and staged through registers (about two prefix blocks'
+// time) after a table of fp64 angles (two more): given an even share that
+// workgroup ended 8 us after the others at 128 nodes and prefix 8192 (43.8
+// against a median of 35), 4 us at 27 nodes and prefix 2048.
+constexpr int kTreeSetup = 2;
+__host__ __device__ inline int tree_extra(int nblocks, int L, int ns) {
+  const int extra = kTreeSetup + nblocks - L / KB, share = nblocks / ns;
+  return extra < share ? extra : share;   // (the last split keeps a block)
+}
+__device__ __forceinline__ int split_begin(int k, int ns, int nblocks, int extra) {
+  return k < ns ? static_cast<int>(static_cast<unsigned>(k) * static_cast<unsigned>(nblocks + extra) / ns)
+                : nblocks;
+}
+
+// A batch of several sequences shares one blocks-per-split target t: sequence
+// b, with H_b streams (KV heads x query groups) of nb_b blocks, takes
+// ns_b(t) = ceil(nb_b / t) splits (clipped to [1, split_bound]).  Every
+// workgroup costs its blocks and a fixed part, and the chip runs `slots` of
+// them at a time, so the target minimises
+//   rounds(sum H_b ns_b(t)) * (kWgFixed + t)  (+ kMergeCost when any is split)
+// over kTargets candidates: the last one splits nothing (t = the longest),
+// the others are multiples of the even share work / slots, from half of it
+// (two rounds) up.  A fixed number of workgroups per CU instead (three, at two
+// resident) left the second round half empty: eight GQA sequences 103 us
+// against 88, at prefixes up to 4096 62 us a call against 48.
+constexpr int kTargets = 16;
+constexpr int kWgFixed = 6;      // a workgroup's fixed part, in blocks (8 us at 1.3-1.7 us a block)
+constexpr int kMergeCost = 4;    // the merge kernel, in blocks
+__host__ __device__ inline int target_sixteenths(int k) {   // of the even share
+  constexpr unsigned long long lo = 0x1413121110'0a0908ull;   // 8 9 10 16 17 18 19 20
+  constexpr unsigned long long hi = 0x60402820'1e1c1816ull;   // 22 24 28 30 32 40 64 96
+  return static_cast<int>((k < 8 ? lo >> (8 * k) : hi >> (8 * (k - 8))) & 0xff);
+}
+__host__ __device__ inline int batch_target(int k, long long work, int nb_max, int slots) {
+  if (k == kTargets - 1) return nb_max > 1 ? nb_max : 1;
+  const long long t = (work * target_sixteenths(k) + 16LL * slots - 1) / (16LL * slots);
+  return static_cast<int>(t > kMinBlocksPerSplit ? (t < nb_max ? t : nb_max) : kMinBlocksPerSplit);
+}
+__host__ __device__ inline int batch_splits(int nb, int t) {
+  const int ns = (nb + t - 1) / t, bound = split_bound(nb);
+  return ns < 1 ? 1 : (ns > bound ? bound : ns);
+}
+// One key per candidate: the smallest wins (the lowest candidate among equals).
+__host__ __device__ inline unsigned long long batch_cost(int k, int t, long long items, bool split,
+                                                         int slots) {
+  const long long rounds = (items + slots - 1) / slots;
+  return (static_cast<unsigned long long>(rounds * (kWgFixed + t) + (split ? kMergeCost : 0)) << 8) | k;
+}
+// Most workgroups a planned batch can have (padding aside) when its streams
+// number at most `streams`: the two-round candidates are allowed only where
+// the streams alone nearly fill the chip, and a split count is below
+// nb / t + 1, so the items stay below work / t + streams.
+__host__ __device__ inline bool two_rounds(long long streams_bound, int slots) {
+  return 4 * streams_bound > 3LL * slots;
 }
 
 // ----------------------------------------------------------- descriptors --
@@ -123,8 +171,7 @@ struct SeqPlan {
   const int* depth;        // [T]
   int T, L, row0;          // nodes, prefix length, first row in the concatenated q / out
   int D;                   // depth of the tree's deepest node
-  int rows_pad, nqt, nqg, nsplit, bps;   // padded rows, query tiles, query groups, splits
-  int nt;                  // query tiles per workgroup the call's plan gives it
+  int rows_pad, nqt, nqg, nsplit;   // padded rows, query tiles, query groups, splits
   int item0;               // first attend workgroup of the sequence
   int merge0;              // first merge block of the sequence
   long long part_off;      // row offset of its split partials
@@ -140,9 +187,9 @@ struct BatchArgs {
   SeqPlan s[kMaxSeqs];
   // device-planned batch: sequence b's tree, prefix length and first row
   // come from device arrays (topo_dev[b], len_dev[b], row_off_dev[b]); the
-  // host fixed its caches and its grid, merge and partial ranges (at strides
-  // sized for the bank's largest plan), and every workgroup derives the
-  // plan the host would have made (plan_call) from those arrays
+  // host fixed its caches and partial range (at strides sized for the bank's
+  // largest plan), and every workgroup derives the plan the host would have
+  // made (plan_call), its own place in it included, from those arrays
   const int32_t* topo_dev;
   const int32_t* len_dev;
   const int32_t* row_off_dev;   // [B + 1]
@@ -157,7 +204,7 @@ struct BatchArgs {
   const DevTopo* topos;
   const uint8_t* arena;
   int cus;
-  int nt;                  // query tiles per workgroup of the launched kernel (1 or 2)
+  int two_rounds;          // device-planned batch: two_rounds() of the streams the host can bound
   int B, G, Hq, Hkv, cap;
   float scale_log2;
   double theta;            // rotation base (0: no rotation)
@@ -183,6 +230,9 @@ __device__ __forceinline__ int seq_of(const BatchArgs& p, int x, F first) {
   return __popcll(__ballot(owns)) - 1;
 }
 
+// Rows a merge block covers (a half-wavefront each).
+constexpr int kMergeRows = 8;
+
 // Plan of sequence b: the host's, or -- for a device-planned call -- the
 // plan the host would make for the tree and prefix length the device holds
 // (same arithmetic), with the caches the host passed.
@@ -207,28 +257,35 @@ __device__ __forceinline__ SeqPlan resolve(const BatchArgs& p, int b) {
   q.row0 = 0;
   q.rows_pad = rows_padded(p.G, q.T);
   q.nqt = q.rows_pad / kQTile;
-  q.nqg = query_groups(q.nqt, tree_tiles(p.G, q.T));
+  q.nqg = query_groups(q.nqt);
   const int nblocks = (q.L + q.T + KB - 1) / KB;
-  const int ns = t->splits[split_bound(nblocks)];   // = split_single(nblocks, Hkv * nqg, cus * wg_per_cu)
-  q.bps = (nblocks + ns - 1) / ns;
-  q.nsplit = (nblocks + q.bps - 1) / q.bps;
+  q.nsplit = t->splits[split_bound(nblocks)];   // = split_single(nblocks, Hkv * nqg, cus)
   q.item0 = 0;
   q.merge0 = 0;
   q.part_off = 0;
   return q;
 }
 
-// Plan of sequence b of a device-planned batch.  Lane i of each wavefront
-// reads sequence i's entries; a sequence whose tree index lies outside the
-// bank, whose prefix length is negative or leaves no room for its tree in
-// the cache, or whose tree rows [row_off[b], row_off[b] + T) do not lie in
-// [row_off[b], row_off[b + 1]) and the row capacity has no work (T = 0) and
-// counts for nothing in the batch plan.
-// The rest is plan_call's arithmetic: the batch's tile count is the largest
-// any sequence needs, and a batch of several shares one blocks-per-split
-// target.  Called by whole wavefronts.
-__device__ __forceinline__ SeqPlan resolve_batch(const BatchArgs& p, int b) {
-  SeqPlan q = p.s[b];   // caches and the fixed ranges
+__device__ __forceinline__ long long uniform(long long x) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<int>(x));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<int>(x >> 32));
+  return static_cast<long long>((static_cast<unsigned long long>(hi) << 32) | lo);
+}
+
+// The sequence that owns index x of a device-planned batch's attend or merge
+// grid (MERGE), its plan included; T = 0 for an index past the last.  Lane i
+// of each wavefront reads sequence i's entries; a sequence whose tree index
+// lies outside the bank, whose prefix length is negative or leaves no room
+// for its tree in the cache, or whose tree rows [row_off[b], row_off[b] + T)
+// do not lie in [row_off[b], row_off[b + 1]) and the row capacity has no work
+// (T = 0) and counts for nothing in the batch plan.
+// The rest is plan_call's arithmetic, the grid ranges a prefix sum over the
+// sequences, so that the grid is as long as the plan (the host bounds it) and
+// not as long as the largest plan of every sequence: those grids' empty
+// workgroups took as long as the attention (185 us a call against 109
+// planned on the host).  Called by whole wavefronts.
+template <bool MERGE>
+__device__ __forceinline__ SeqPlan resolve_batch(const BatchArgs& p, int x) {
   const int lane = threadIdx.x & 63;
   int tr = -1, L = -1, r0 = -1, r1 = -1;
   if (lane < p.B) {
@@ -247,68 +304,104 @@ __device__ __forceinline__ SeqPlan resolve_batch(const BatchArgs& p, int b) {
   const bool ok = named && L >= 0 && static_cast<long long>(L) + T <= p.cap && r0 >= 0 &&
                   end <= r1 && end <= p.rows_cap;
   if (!ok) T = 0;
-  const int nblocks = T ? (L + T + KB - 1) / KB : 0;
-  int nt = T ? tree_tiles(p.G, T) : 1;
+  const int nb = T ? (L + T + KB - 1) / KB : 0;
+  const int rows_pad = rows_padded(p.G, T);
+  const int nqg = query_groups(rows_pad / kQTile);
+  const int H = p.Hkv * nqg;
+  int ns = 1;
+  const int slots = p.cus * kWgPerCu;
+  if (p.B == 1) {
+    if (T) ns = split_single(nb, H, p.cus);
+  } else {
+    // lane k (mod 16) weighs candidate k; the four lanes of a candidate take
+    // every fourth sequence
+    static_assert(kMaxSeqs == 16 && kTargets == 16, "16 lanes hold the sequences, 16 the candidates");
+    long long work = static_cast<long long>(H) * nb;
+    int nb_max = nb;
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) nt = max(nt, __shfl_xor(nt, off, 64));
-  long long work =
-      T ? static_cast<long long>(p.Hkv) * query_groups(rows_padded(p.G, T) / kQTile, nt) * nblocks
-        : 0;
+    for (int off = 8; off >= 1; off >>= 1) {
+      work += __shfl_xor(work, off, 64);
+      nb_max = max(nb_max, __shfl_xor(nb_max, off, 64));
+    }
+    work = uniform(work);   // (lane 0's 16 lanes hold every sequence)
+    nb_max = __builtin_amdgcn_readfirstlane(nb_max);
+    const int k = lane & 15;
+    const int t = batch_target(k, work, nb_max, slots);
+    long long items = 0;
+    int split = 0;
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) work += __shfl_xor(work, off, 64);
-  const int Tb = __shfl(T, b, 64);
-  if (Tb == 0) {
+    for (int u = 0; u < kMaxSeqs / 4; ++u) {
+      const int b = (lane >> 4) + 4 * u;
+      const int nbb = __shfl(nb, b, 64), Hb = __shfl(H, b, 64);
+      const int n = batch_splits(nbb, t);
+      items += static_cast<long long>(Hb) * n;
+      split |= Hb > 0 && n > 1;
+    }
+#pragma unroll
+    for (int off = 16; off <= 32; off <<= 1) {
+      items += __shfl_xor(items, off, 64);
+      split |= __shfl_xor(split, off, 64);
+    }
+    unsigned long long cost = batch_cost(k, t, items, split, slots);
+    if (target_sixteenths(k) < 16 && !p.two_rounds) cost = ~0ull;
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) {
+      const unsigned long long o = __shfl_xor(cost, off, 64);
+      cost = o < cost ? o : cost;
+    }
+    const int best = __builtin_amdgcn_readfirstlane(static_cast<int>(cost & 0xff));
+    ns = batch_splits(nb, __builtin_amdgcn_readlane(t, best));
+  }
+  // this sequence's range of the grid, and the sequence x lies in
+  const int len = MERGE ? (ns > 1 ? (p.Hkv * p.G * T + kMergeRows - 1) / kMergeRows : 0)
+                        : (T ? (p.Hkv * ns + 7) / 8 * 8 * nqg : 0);
+  int last = len;   // inclusive prefix sum
+#pragma unroll
+  for (int off = 1; off < kMaxSeqs; off <<= 1) {
+    const int o = __shfl_up(last, off, 64);
+    if (lane >= off) last += o;
+  }
+  const unsigned long long past = __ballot(lane < p.B && x >= last);
+  const int b = __popcll(past);
+  SeqPlan q = p.s[b < p.B ? b : 0];   // caches and the partial range
+  if (b >= p.B) {
     q.T = 0;
-    q.L = 0;
-    q.nsplit = 1;
-    q.nqt = 0;
-    q.nqg = 0;
-    q.nt = nt;
     return q;
   }
-  const int trb = __shfl(tr, b, 64);
-  const TreeHdr& h = p.trees[trb];
-  q.T = Tb;
-  q.L = __shfl(L, b, 64);
-  q.row0 = __shfl(r0, b, 64);
+  // (readlane: the plan stays in scalar registers, and with it the buffer
+  // descriptors of the copies; through shuffles a block took 1.0 us, not 0.8)
+  auto at = [&](int v) { return __builtin_amdgcn_readlane(v, b); };
+  const TreeHdr& h = p.trees[at(tr)];
+  q.T = at(T);
+  q.L = at(L);
+  q.row0 = at(r0);
   q.D = h.D;
   q.mask = reinterpret_cast<const uint32_t*>(p.arena + h.off_mask);
   q.depth = reinterpret_cast<const int*>(p.arena + h.off_depth);
-  q.nt = nt;
-  q.rows_pad = rows_padded(p.G, q.T);
+  q.rows_pad = at(rows_pad);
   q.nqt = q.rows_pad / kQTile;
-  q.nqg = query_groups(q.nqt, nt);
-  const int nb = (q.L + q.T + KB - 1) / KB;
-  int ns;
-  if (p.B == 1) {
-    ns = split_single(nb, p.Hkv * q.nqg, p.cus * wg_per_cu(nt));
-  } else {
-    const long long per_wg = (work + kBatchWgPerCu * p.cus - 1) / (kBatchWgPerCu * p.cus);
-    const int target_bps = static_cast<int>(per_wg > kMinBlocksPerSplit ? per_wg : kMinBlocksPerSplit);
-    ns = (nb + target_bps - 1) / target_bps;
-    const int bound = split_bound(nb);
-    ns = ns < 1 ? 1 : (ns > bound ? bound : ns);
-  }
-  q.bps = (nb + ns - 1) / ns;
-  q.nsplit = (nb + q.bps - 1) / q.bps;
+  q.nqg = at(nqg);
+  q.nsplit = at(ns);
+  q.item0 = q.merge0 = at(last - len);
   return q;
+}
+
+// Plan of the sequence that owns index x of the attend or (MERGE) merge grid.
+template <bool DEVB, bool MERGE>
+__device__ __forceinline__ SeqPlan plan_of(const BatchArgs& p, int x) {
+  if constexpr (DEVB)
+    return resolve_batch<MERGE>(p, x);
+  else
+    return resolve(p, seq_of(p, x, [](const SeqPlan& q) { return MERGE ? q.merge0 : q.item0; }));
 }
 
 // ------------------------------------------------------------------ RoPE --
 
-// Angles of a tree's positions: tab[d * 64 + c] = (cos, sin) of the turn of
-// pair (c, c + 64) at position L + d, d = 0..D, in fp64 (pos * freq[c],
-// freq[c] = theta^(-2c/d) from the host), followed by the same table in
-// fp32 (for the queries), filled by the workgroup's threads (a multiple of
-// 64: each keeps one pair's frequency).  The tables live in the kernel's
-// dynamic LDS, sized by the host for the deepest tree of the launch.
+// Angles of a tree's positions: the turn of pair (c, c + 64) at position
+// L + d, d = 0..D, in fp64 (pos * freq[c], freq[c] = theta^(-2c/d) from the
+// host), tabulated as (cos, sin) by the workgroup's threads (a multiple of
+// 64: each keeps one pair's frequency).
 constexpr int kRopePairs = HD / 2;
-inline size_t rope_lds_bytes(int D, double theta) {
-  return theta > 0.0 ? static_cast<size_t>(D + 1) * kRopePairs * (sizeof(double2) + sizeof(float2)) : 0;
-}
-__device__ __forceinline__ float2* rope_table_f32(double2* tab, int D) {
-  return reinterpret_cast<float2*>(tab + (D + 1) * kRopePairs);
-}
 inline void set_rope(BatchArgs& a, float rope_theta) {
   a.theta = static_cast<double>(rope_theta);
   for (int c = 0; c < kRopePairs; ++c) a.freq[c] = a.theta > 0.0 ? std::pow(a.theta, -2.0 * c / HD) : 0.0;
@@ -359,17 +452,18 @@ __device__ __forceinline__ void rope_table(int D, int L, double f, F put) {
 }
 
 // Turns the 8 pairs (c0 + e, c0 + e + 64), e < 8, whose halves lo / hi hold
-// (bf16), by the angles at t[c0 .. c0 + 7] (t = the position's table row):
+// (bf16), by the angles at t[0 .. 7] (t = the position's table row at c0, its
+// eight entries at index ^ swz, so that the lanes of a row read other banks):
 // lo cos - hi sin and hi cos + lo sin in fp64 (each product rounded, then
 // the sum: no fused multiply-add), each rounded to bf16 once.
-__device__ __forceinline__ void rope_pairs(u32x4& lo, u32x4& hi, const double2* t) {
+__device__ __forceinline__ void rope_pairs(u32x4& lo, u32x4& hi, const double2* t, int swz) {
 #pragma clang fp contract(off)
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
     uint32_t nl = 0u, nh = 0u;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const double2 a = t[2 * w + h];
+      const double2 a = t[(2 * w + h) ^ swz];
       const double x = bf16_to_f64(static_cast<uint16_t>(lo[w] >> (16 * h)));
       const double y = bf16_to_f64(static_cast<uint16_t>(hi[w] >> (16 * h)));
       nl |= f64_to_bf16_rne(x * a.x - y * a.y) << (16 * h);
@@ -380,13 +474,15 @@ __device__ __forceinline__ void rope_pairs(u32x4& lo, u32x4& hi, const double2* 
   }
 }
 
-// The same turn in fp32 with fp32 angles, rounded to bf16 by the hardware
+// The same turn of pairs c0 .. c0 + 7 in fp32 with fp32 angles (pair c at
+// t[c ^ swz]: lanes at other depths read other banks), rounded to bf16 by the hardware
 // (for the queries, which only enter bf16 products: the cache keeps the
 // fp64 form's keys).
-__device__ __forceinline__ void rope_pairs_f32(u32x4& lo, u32x4& hi, const float2* t) {
+__device__ __forceinline__ void rope_pairs_f32(u32x4& lo, u32x4& hi, const float2* t, int c0, int swz) {
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    const float2 a0 = t[2 * w], a1 = t[2 * w + 1];
+    const float4 a = *reinterpret_cast<const float4*>(t + ((c0 + 2 * w) ^ swz));   // (swz is even)
+    const float2 a0 = make_float2(a.x, a.y), a1 = make_float2(a.z, a.w);
     const float x0 = bf16_lo(lo[w]), x1 = bf16_hi(lo[w]);
     const float y0 = bf16_lo(hi[w]), y1 = bf16_hi(hi[w]);
     lo[w] = __builtin_bit_cast(uint32_t, __builtin_convertvector(
@@ -396,479 +492,10 @@ __device__ __forceinline__ void rope_pairs_f32(u32x4& lo, u32x4& hi, const float
   }
 }
 
-// One half of a pair whose other half sits in lane ^ 8 (a key row loaded as
-// 16 lanes x 16 bytes: chunk m holds dims 8m .. 8m + 7): the rotated chunk,
-// only this lane's half computed -- mine cos - other sin for the first half,
-// mine cos + other sin for the second (the same rounded steps as
-// rope_pairs).  Every lane must call it (shuffles); `on` selects the lanes
-// that rotate.
-__device__ __forceinline__ u32x4 rope_half(const u32x4& mine, int m, bool on, const double2* t) {
-#pragma clang fp contract(off)
-  u32x4 other;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) other[w] = static_cast<uint32_t>(__shfl_xor(static_cast<int>(mine[w]), 8, 64));
-  if (!on) return mine;
-  const double2* a = t + 8 * (m & 7);
-  u32x4 out;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    uint32_t r = 0u;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const double2 cs = a[2 * w + h];
-      const double x = bf16_to_f64(static_cast<uint16_t>(mine[w] >> (16 * h)));
-      const double y = bf16_to_f64(static_cast<uint16_t>(other[w] >> (16 * h)));
-      const double sn = m < 8 ? -cs.y : cs.y;
-      r |= f64_to_bf16_rne(x * cs.x + y * sn) << (16 * h);
-    }
-    out[w] = r;
-  }
-  return out;
-}
-
 // ---------------------------------------------------------------- attend --
 
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// One query tile per workgroup (trees of up to 32 query rows per KV head);
-// the per-tile state below is written for NT tiles held by every wave.
-// DEVB: a device-planned batch (its own instantiation, so the host-planned
-// and single device-planned forms keep their registers).
-template <bool DEVB>
-__global__ __launch_bounds__(kAttnThreads) void tree_attn_kernel(BatchArgs p) {
-  constexpr int NT = 1;
-  // blockIdx -> sequence, then (kv head, split) group and query-tile group;
-  // the query groups of one (head, split) land on the same XCD (dispatch is
-  // round-robin over 8 XCDs and every sequence's range starts at a multiple
-  // of 8), so their K/V reads share that XCD's L2.
-  const int b = seq_of(p, static_cast<int>(blockIdx.x), [](const SeqPlan& q) { return q.item0; });
-  const SeqPlan sq = DEVB ? resolve_batch(p, b) : resolve(p, b);
-  if (sq.T == 0) return;
-  if (DEVB ? sq.nt != NT : (p.dev && tree_tiles(p.G, sq.T) != NT)) return;   // another instance's
-  const int bid = blockIdx.x - sq.item0;
-  const int qg = (bid >> 3) % sq.nqg;
-  const int gc = ((bid >> 3) / sq.nqg) * 8 + (bid & 7);
-  if (gc >= p.Hkv * sq.nsplit) return;
-  const int g = gc / sq.nsplit, split = gc % sq.nsplit;
-  const int T = sq.T, L = sq.L, nkeys = sq.L + sq.T, rows_pad = sq.rows_pad;
-  const int nsplit = sq.nsplit;
-  const int qt0 = qg * NT;   // first query tile of the group
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int li = lane & 31, lh = lane >> 5;
-  const int GT = p.G * T;
-  constexpr int QR = NT * kQTile;   // query rows of a group
-
-  // LDS: the tiles' Q fragments and per-wave V^T tiles during the loop, one
-  // region reused for the wave merge after it
-  constexpr int kQfBytes = NT * 8 * 64 * 16;
-  constexpr int kVtBytes = HD * VT_LD * 2;                           // 9216
-  constexpr int OLD = HD + 4;                                         // merge row stride (floats)
-  constexpr int kMergeBytes = 2 * kQTile * OLD * 4;                  // 33792: two wave slots
-  constexpr int kLoopBytes = kQfBytes + kAttnWaves * kVtBytes;
-  constexpr int kLdsBytes = kMergeBytes > kLoopBytes ? kMergeBytes : kLoopBytes;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[kLdsBytes];
-  __shared__ uint32_t s_mask[QR][ENTMTP_MASK_WORDS + 1];
-  __shared__ float s_m[kAttnWaves][QR], s_l[kAttnWaves][QR];
-  __shared__ float s_sc[kAttnWaves][QR];   // each wave's factor to the common max
-  __shared__ float s_M[QR], s_L[QR];        // a row's common max and sum
-  extern __shared__ __attribute__((aligned(16))) double2 s_rope[];   // angles of the tree's positions
-  u32x4 (*s_qf)[8][64] = reinterpret_cast<u32x4 (*)[8][64]>(lds);   // [NT][s][lane]
-  uint32_t* vt = reinterpret_cast<uint32_t*>(lds + kQfBytes + wave * kVtBytes);  // [HD][VT_LD/2]
-
-  const size_t head_off = static_cast<size_t>(g) * p.cap * HD;
-  const uint16_t* kbase = sq.kc + head_off;
-  const uint16_t* vbase = sq.vc + head_off;
-  const float c = p.scale_log2;
-  const int nblocks = (nkeys + KB - 1) / KB;
-  const int blk_lo = split * sq.bps;
-  const int blk_hi = min(nblocks, blk_lo + sq.bps);
-
-  // K/V of one block into registers: prefix keys from the cache, the tree's
-  // keys (slots L and up, not yet rotated) and values from the step's
-  // inputs.  Keys past the end are clamped to the last key (finite data
-  // whose probabilities are zero), so every load is unconditional and the
-  // compiler's wait counts stay exact.
-  auto krow = [&](int key) {
-    return key < L ? kbase + static_cast<size_t>(key) * HD
-                   : p.kt + (static_cast<size_t>(sq.row0 + key - L) * p.Hkv + g) * HD;
-  };
-  auto vrow = [&](int key) {
-    return key < L ? vbase + static_cast<size_t>(key) * HD
-                   : p.vt + (static_cast<size_t>(sq.row0 + key - L) * p.Hkv + g) * HD;
-  };
-  auto load_k = [&](int blk, u32x4 (&kf)[8]) {
-    const int kb = blk * KB;
-    const int key = min(kb + li, nkeys - 1);
-    const uint16_t* kp = krow(key) + 8 * lh;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) kf[s] = *reinterpret_cast<const u32x4*>(kp + 16 * s);
-  };
-  auto load_v = [&](int blk, u32x4 (&va)[4], u32x4 (&vb)[4]) {
-    const int kb = blk * KB;
-    const int last = nkeys - 1;
-    // V: key pairs (2pp, 2pp+1) x 8-dim chunk m
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int u = lane + 64 * k;
-      const int pp = u & 15, m = u >> 4;
-      const int k0 = min(kb + 2 * pp, last), k1 = min(kb + 2 * pp + 1, last);
-      va[k] = *reinterpret_cast<const u32x4*>(vrow(k0) + 8 * m);
-      vb[k] = *reinterpret_cast<const u32x4*>(vrow(k1) + 8 * m);
-    }
-  };
-  // the first query group's workgroups keep the tree's keys and values in
-  // the cache (slots L .. L + T - 1) for the steps after this one
-  const bool keeper = qg == 0;
-  uint16_t* const kc_head = sq.kc + head_off;
-  uint16_t* const vc_head = sq.vc + head_off;
-
-  // Q^T B-operand fragments, the same for the four waves (they split keys,
-  // not queries), staged once in LDS: lane (query li, half lh) of tile t
-  // reads d = 16s + 8lh + e from slot [t][s][lane].  Query row r of KV head
-  // g is (head g * G + r / T, node r % T); thread (s, ln) loads chunks s and
-  // s + 4 of its row (the two halves of pairs 16s + 8lh + e).  These small
-  // loads (and the masks, the depth and the pair frequency) are requested
-  // first and unconditionally (rows past the tree read row 0 and are never
-  // stored): behind the waves' first K/V blocks they would wait for every
-  // workgroup's burst.
-  static_assert(NT * 4 * 64 == kAttnThreads, "one thread per pair of Q chunks");
-  const int qs = (tid >> 6) & 3, qhl = (tid >> 5) & 1;
-  const int qrow = qt0 * kQTile + li;
-  const bool qlive = qrow < GT;
-  const int qnode = qlive ? qrow % T : 0;
-  u32x4 qlo, qhi;
-  {
-    const uint16_t* qp = p.q + (static_cast<size_t>(sq.row0 + qnode) * p.Hq + g * p.G + (qlive ? qrow / T : 0)) * HD +
-                         8 * qhl + 16 * qs;
-    qlo = *reinterpret_cast<const u32x4*>(qp);
-    qhi = *reinterpret_cast<const u32x4*>(qp + HD / 2);
-  }
-  const int qdepth = sq.depth[qnode];
-  static_assert(QR * ENTMTP_MASK_WORDS == kAttnThreads, "one mask word per thread");
-  const int mrow = qt0 * kQTile + tid / ENTMTP_MASK_WORDS;
-  const uint32_t mword = sq.mask[(mrow < GT ? mrow % T : 0) * ENTMTP_MASK_WORDS + tid % ENTMTP_MASK_WORDS];
-  const double freq = p.freq[tid % kRopePairs];
-
-  // the wave's first block is requested before the rest of the prologue, so
-  // its latency overlaps the staging of the queries
-  const bool active = blk_lo + wave < blk_hi;
-  u32x4 kA[8], kB[8], v0[4], v1[4];
-  int cur = blk_lo + wave;
-  if (active) {
-    load_k(cur, kA);
-    load_v(cur, v0, v1);
-  }
-
-  // ancestor masks of the group's query rows (padding rows see every key),
-  // the angle table, and the rotated Q fragments into LDS
-  s_mask[tid / ENTMTP_MASK_WORDS][tid % ENTMTP_MASK_WORDS] = mrow < GT ? mword : 0xFFFFFFFFu;
-  const bool rope = p.theta > 0.0;
-  if (rope) {
-    float2* const tab32 = rope_table_f32(s_rope, sq.D);
-    rope_table(sq.D, L, freq, [&](int d, int pr, double2 cs) {
-      s_rope[d * kRopePairs + pr] = cs;
-      tab32[d * kRopePairs + pr] = make_float2(static_cast<float>(cs.x), static_cast<float>(cs.y));
-    });
-    __syncthreads();
-    if (qlive) rope_pairs_f32(qlo, qhi, tab32 + qdepth * kRopePairs + 16 * qs + 8 * qhl);
-  }
-  s_qf[0][qs][lane] = qlive ? qlo : u32x4{0u, 0u, 0u, 0u};
-  s_qf[0][qs + 4][lane] = qlive ? qhi : u32x4{0u, 0u, 0u, 0u};
-  __syncthreads();
-
-  // running (max, sum) per query in base-2 scaled units and the output
-  // accumulators, per tile.  The max is raised lazily: the reference m stays
-  // until a block's maximum exceeds it by more than kLazyLog2, so that the
-  // accumulators are rescaled only a few times per row instead of per block
-  // (probabilities relative to m then reach at most 2^kLazyLog2).
-  float m_run[NT], l_run[NT];
-  f32x16 o[NT][4];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    m_run[t] = -INFINITY;
-    l_run[t] = 0.f;
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[t][ct][r] = 0.f;
-  }
-
-  // a block's V into this wave's V^T tile: word (dim, key pair) packs the
-  // pair's two bf16 values of that dim (and the tree's values into the cache)
-  auto stage_v = [&](int blk, const u32x4 (&va)[4], const u32x4 (&vb)[4]) {
-    if (keeper && blk * KB + KB > L) {
-      const int kb = blk * KB;
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int u = lane + 64 * k;
-        const int pp = u & 15, m = u >> 4;
-        const int k0 = kb + 2 * pp, k1 = k0 + 1;
-        if (k0 >= L && k0 < nkeys) *reinterpret_cast<u32x4*>(vc_head + static_cast<size_t>(k0) * HD + 8 * m) = va[k];
-        if (k1 >= L && k1 < nkeys) *reinterpret_cast<u32x4*>(vc_head + static_cast<size_t>(k1) * HD + 8 * m) = vb[k];
-      }
-    }
-    wave_lds_sync();  // previous block's V^T reads are done
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int u = lane + 64 * k;
-      const int pp = u & 15, m = u >> 4;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const uint32_t a = va[k][w], bw = vb[k][w];
-        // dims 8m + 2w (low halves) and 8m + 2w + 1 (high halves)
-        vt[(8 * m + 2 * w) * (VT_LD / 2) + pp] = __builtin_amdgcn_perm(bw, a, 0x05040100u);
-        vt[(8 * m + 2 * w + 1) * (VT_LD / 2) + pp] = __builtin_amdgcn_perm(bw, a, 0x07060302u);
-      }
-    }
-  };
-
-  // scores of one tile -> its probabilities as the B operand of the PV
-  // product (bf16), with the lazy rescale of the tile's accumulators.
-  // Lane (query li, half lh) holds keys n = 8*(r/4) + 4*lh + r%4 of the block.
-  auto softmax = [&](int t, f32x16& sacc, int kb, bool plain, bf16x8 (&pf)[2]) {
-    float bmax = -INFINITY;
-    if (plain) {   // the whole block lies in the prefix: every key is visible
-#pragma unroll
-      for (int r = 0; r < 16; ++r) bmax = fmaxf(bmax, sacc[r]);
-    } else {
-      // 32-key window of the query's visibility: prefix keys, then the
-      // ancestor bitmask from position L on
-      uint32_t win = 0xFFFFFFFFu;
-      const int rel = kb - L;
-      const uint32_t* mrow = s_mask[t * kQTile + li];
-      if (rel < 0) {
-        const int npre = -rel;
-        win = (0xFFFFFFFFu >> (32 - npre)) | (mrow[0] << npre);
-      } else {
-        const int wi = rel >> 5, sh = rel & 31;
-        const uint32_t lo = mrow[wi];
-        const uint32_t hi = wi + 1 < ENTMTP_MASK_WORDS ? mrow[wi + 1] : 0u;
-        win = sh ? (lo >> sh) | (hi << (32 - sh)) : lo;
-      }
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int n = 8 * (r >> 2) + 4 * lh + (r & 3);
-        const bool vis = ((win >> n) & 1u) && (kb + n < nkeys);
-        sacc[r] = vis ? sacc[r] : -INFINITY;
-        bmax = fmaxf(bmax, sacc[r]);
-      }
-    }
-    bmax = fmaxf(bmax, __shfl_xor(bmax, 32, 64));
-    const float mb = bmax * c;   // -inf stays -inf (c > 0)
-    const bool need = mb > m_run[t] + kLazyLog2;
-    if (__any(need)) {   // uniform branch: rare once the row maximum has settled
-      const float mn = need ? mb : m_run[t];
-      const float alpha = !need ? 1.f : (m_run[t] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[t] - mn));
-      l_run[t] *= alpha;
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[t][ct][r] *= alpha;
-      m_run[t] = mn;
-    }
-    // with m still -inf every key so far is hidden from the query: p = 0
-    const float mneg = m_run[t] == -INFINITY ? 0.f : -m_run[t];
-    float pr[16];
-    float rsum = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      pr[r] = __builtin_amdgcn_exp2f(fmaf(sacc[r], c, mneg));
-      rsum += pr[r];
-    }
-    rsum += __shfl_xor(rsum, 32, 64);
-    l_run[t] += rsum;
-    // P^T as B operand: step u covers keys 16u..16u+15; element e of lane
-    // (query li, half lh) is key 16u + 4lh + e (e < 4) or 16u + 8 + 4lh + e-4
-    // -- exactly accumulator entries 8u .. 8u+7.
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      u32x4 w;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        w[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(
-                                               (f32x2{pr[8 * u + 2 * e], pr[8 * u + 2 * e + 1]}), bf16x2));
-      pf[u] = as_bf16x8(w);
-    }
-  };
-
-  // the block's scores, softmax and P V for the group's tiles (V from the
-  // staged tile, each V^T fragment read once for all tiles)
-  auto attend = [&](int blk, u32x4 (&kf)[8]) {
-    const int kb = blk * KB;
-    const bool plain = kb + KB <= L;
-    if (!plain) {   // the tree's keys: rotate, and keep them in the cache
-      const int key = min(kb + li, nkeys - 1);
-      if (key >= L) {
-        if (rope) {
-          const double2* tr = s_rope + sq.depth[key - L] * kRopePairs + 8 * lh;
-#pragma unroll
-          for (int s = 0; s < 4; ++s) rope_pairs(kf[s], kf[s + 4], tr + 16 * s);
-        }
-        if (keeper && kb + li < nkeys) {
-#pragma unroll
-          for (int s = 0; s < 8; ++s)
-            *reinterpret_cast<u32x4*>(kc_head + static_cast<size_t>(key) * HD + 8 * lh + 16 * s) = kf[s];
-        }
-      }
-    }
-    f32x16 sacc[NT];
-    bf16x8 pf[NT][2];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      // S^T[key][query] = K Q^T
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[t][r] = 0.f;
-#pragma unroll
-      for (int s = 0; s < 8; ++s)
-        sacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf[s]), as_bf16x8(s_qf[t][s][lane]),
-                                                        sacc[t], 0, 0, 0);
-    }
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      softmax(t, sacc[t], kb, plain, pf[t]);
-    }
-    wave_lds_sync();  // V^T tile written by every lane
-    // O^T[dim][query] += V^T P^T; A operand lane (dim li of tile ct, half lh)
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      const uint32_t* row = vt + (32 * ct + li) * (VT_LD / 2);
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const uint2 x0 = *reinterpret_cast<const uint2*>(row + 8 * u + 2 * lh);
-        const uint2 x1 = *reinterpret_cast<const uint2*>(row + 8 * u + 4 + 2 * lh);
-        const u32x4 w = {x0.x, x0.y, x1.x, x1.y};
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-          o[t][ct] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(w), pf[t][u], o[t][ct], 0, 0, 0);
-      }
-    }
-  };
-
-  // K two deep (block b+4 streams in while block b is multiplied); V one
-  // deep, the next block's loads issued as soon as this block's V is in its
-  // LDS tile.  (The loads after a wave's last block re-read that block, an
-  // L2 hit.)
-  if (active) {
-    while (true) {
-      const int nb = cur + kAttnWaves;
-      const int nbc = nb < blk_hi ? nb : cur;
-      load_k(nbc, kB);
-      stage_v(cur, v0, v1);
-      load_v(nbc, v0, v1);
-      attend(cur, kA);
-      if (nb >= blk_hi) break;
-      const int nb2 = nb + kAttnWaves;
-      const int nb2c = nb2 < blk_hi ? nb2 : nb;
-      load_k(nb2c, kA);
-      stage_v(nb, v0, v1);
-      load_v(nb2c, v0, v1);
-      attend(nb, kB);
-      if (nb2 >= blk_hi) break;
-      cur = nb2;
-    }
-  }
-
-  // ---- merge the four waves, tile by tile: each wave rescales to the
-  // common reference max; waves 2 and 3 hand their sums to 0 and 1 through
-  // two LDS slots, 0 and 1 write the pair sums back, and all threads combine
-  // the two slots into the output (float4 rows, no more LDS than the loop's)
-  __syncthreads();  // every wave is done with its Q fragments and V^T tile
-  if (lh == 0) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      s_m[wave][t * kQTile + li] = m_run[t];
-      s_l[wave][t * kQTile + li] = l_run[t];
-    }
-  }
-  __syncthreads();
-  // per row, once: the common max, each wave's factor to it, and the sum
-  if (tid < QR) {
-    float M = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < kAttnWaves; ++w) M = fmaxf(M, s_m[w][tid]);
-    float lsum = 0.f;
-#pragma unroll
-    for (int w = 0; w < kAttnWaves; ++w) {
-      const float sc = (s_m[w][tid] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(s_m[w][tid] - M);
-      s_sc[w][tid] = sc;
-      lsum += s_l[w][tid] * sc;
-    }
-    s_M[tid] = M;
-    s_L[tid] = lsum;
-  }
-  __syncthreads();
-  float* ored = reinterpret_cast<float*>(lds);  // [slot][query][OLD]
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const float myscale = s_sc[wave][t * kQTile + li];
-    // lane (query li, half lh) holds dims 32ct + 8j + 4lh + i in o[t][ct][4j + i]
-    auto slot_at = [&](int slot, int ct, int j) {
-      return reinterpret_cast<float4*>(ored + (slot * kQTile + li) * OLD + 32 * ct + 8 * j + 4 * lh);
-    };
-    if (t > 0) __syncthreads();   // the previous tile's slots are read out
-    if (wave >= 2) {
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          *slot_at(wave - 2, ct, j) = make_float4(o[t][ct][4 * j] * myscale, o[t][ct][4 * j + 1] * myscale,
-                                                  o[t][ct][4 * j + 2] * myscale, o[t][ct][4 * j + 3] * myscale);
-    }
-    __syncthreads();
-    if (wave < 2) {
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          float4* sl = slot_at(wave, ct, j);
-          const float4 x = *sl;
-          *sl = make_float4(x.x + o[t][ct][4 * j] * myscale, x.y + o[t][ct][4 * j + 1] * myscale,
-                            x.z + o[t][ct][4 * j + 2] * myscale, x.w + o[t][ct][4 * j + 3] * myscale);
-        }
-    }
-    __syncthreads();
-    // thread -> (query q, four dims): 32 x 32 float4 items, four per thread
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int x = tid + kAttnThreads * i;
-      const int q = x >> 5, d4 = 4 * (x & 31);
-      const int row = (qt0 + t) * kQTile + q;
-      if (row >= GT) continue;
-      const int sr = t * kQTile + q;
-      const float Mq = s_M[sr], lsum = s_L[sr];
-      const float4 s0 = *reinterpret_cast<const float4*>(ored + q * OLD + d4);
-      const float4 s1 = *reinterpret_cast<const float4*>(ored + (kQTile + q) * OLD + d4);
-      const float4 os = make_float4(s0.x + s1.x, s0.y + s1.y, s0.z + s1.z, s0.w + s1.w);
-      if (nsplit == 1) {
-        const int gh = row / T, node = row % T;
-        const int h = g * p.G + gh;
-        uint2 pk;
-        pk.x = f32_to_bf16_rne(os.x / lsum) | (f32_to_bf16_rne(os.y / lsum) << 16);
-        pk.y = f32_to_bf16_rne(os.z / lsum) | (f32_to_bf16_rne(os.w / lsum) << 16);
-        *reinterpret_cast<uint2*>(p.out + (static_cast<size_t>(sq.row0 + node) * p.Hq + h) * HD + d4) = pk;
-      } else {
-        const size_t prow = sq.part_off + (static_cast<size_t>(split) * p.Hkv + g) * rows_pad + row;
-        const float il = lsum > 0.f ? 1.f / lsum : 0.f;   // 0: no key of the split is visible
-        uint2 pk;
-        pk.x = f32_to_bf16_rne(os.x * il) | (f32_to_bf16_rne(os.y * il) << 16);
-        pk.y = f32_to_bf16_rne(os.z * il) | (f32_to_bf16_rne(os.w * il) << 16);
-        *reinterpret_cast<uint2*>(p.part_o + prow * HD + d4) = pk;
-        if (d4 == 0) {
-          p.part_ml[prow * 2 + 0] = Mq;
-          p.part_ml[prow * 2 + 1] = lsum;
-        }
-      }
-    }
-  }
-}
-
-// Four query tiles per workgroup, one per wave (trees with more than 32
-// query rows per KV head; waves past the tree's last tile only load).  The
+// Four query tiles per workgroup, one per wave (waves past the tree's last
+// tile only load).  The
 // four waves walk the same key blocks, which reach LDS by direct global->LDS
 // copies (no registers, no LDS stores) into a ring of kRing slots, one
 // barrier per block; K and V lie there as 256-byte rows, their 16-byte chunks
@@ -907,11 +534,13 @@ __device__ __forceinline__ int k_swz(int r) { return r & 15; }
 __device__ __forceinline__ int v_swz(int r) { return 4 * (r & 3); }
 
 template <bool DEVB>
-__global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs p) {
-  const int b = seq_of(p, static_cast<int>(blockIdx.x), [](const SeqPlan& q) { return q.item0; });
-  const SeqPlan sq = DEVB ? resolve_batch(p, b) : resolve(p, b);
+__global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_kernel(BatchArgs p) {
+  // blockIdx -> sequence, then (kv head, split) group and query-tile group;
+  // the query groups of one (head, split) land on the same XCD (dispatch is
+  // round-robin over 8 XCDs and every sequence's range starts at a multiple
+  // of 8), so their K/V reads share that XCD's L2.
+  const SeqPlan sq = plan_of<DEVB, false>(p, static_cast<int>(blockIdx.x));
   if (sq.T == 0) return;
-  if (DEVB ? sq.nt != 4 : (p.dev && tree_tiles(p.G, sq.T) != 4)) return;   // another instance's
   const int bid = blockIdx.x - sq.item0;
   const int qg = (bid >> 3) % sq.nqg;
   const int gc = ((bid >> 3) / sq.nqg) * 8 + (bid & 7);
@@ -940,8 +569,9 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
   uint16_t* const vc_head = sq.vc + head_off;
   const float c = p.scale_log2;
   const int nblocks = (nkeys + KB - 1) / KB;
-  const int blk_lo = split * sq.bps;
-  const int blk_hi = min(nblocks, blk_lo + sq.bps);
+  const int extra = tree_extra(nblocks, L, nsplit);
+  const int blk_lo = split_begin(split, nsplit, nblocks, extra);
+  const int blk_hi = split_begin(split + 1, nsplit, nblocks, extra);
   const int nb = blk_hi - blk_lo;
   const bool rope = p.theta > 0.0;
   // the first query group's workgroups keep the tree's keys (rotated) and
@@ -981,7 +611,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
   // row (the two halves of pairs 8 cc .. 8 cc + 7), rotates a tree key, and
   // the keeper writes it and its value to the cache.  (In the main loop an
   // ordinary load or an LDS store would wait for every copy in flight.)
-  auto tab64 = [&](int d) {   // angles at depth d, 16 depths a slot
+  auto tab64 = [&](int d) {   // angles at depth d (pair c at tab64_at), 16 depths a slot
     return reinterpret_cast<double2*>(d < 16 ? slot2 : slot3) + (d & 15) * kRopePairs;
   };
   static_assert(16 * kRopePairs * sizeof(double2) <= kRingSlot && ENTMTP_D_MAX < 32, "the angles fit in two slots");
@@ -1003,7 +633,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
   auto tree_stage = [&](uint8_t* slot, TreeRegs& t, int i) {
     const int key = (blk_lo + i) * KB + trow;
     if (key >= L && key < nkeys) {
-      if (rope) rope_pairs(t.k0, t.k1, tab64(s_depth[key - L]) + 8 * tcc);
+      if (rope) rope_pairs(t.k0, t.k1, tab64(s_depth[key - L]) + 8 * tcc, tcc & 7);
       if (keeper) {
         uint16_t* kd = kc_head + static_cast<size_t>(key) * HD + 8 * tcc;
         uint16_t* vd = vc_head + static_cast<size_t>(key) * HD + 8 * tcc;
@@ -1052,7 +682,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
   float2* const tab32 = reinterpret_cast<float2*>(slot3);
   static_assert((ENTMTP_D_MAX + 1) * kRopePairs * sizeof(float2) <= kRingSlot, "the angles fit in a slot");
   if (rope) rope_table(sq.D, L, freq, [&](int d, int pr, double2 cs) {
-    tab32[d * kRopePairs + pr] = make_float2(static_cast<float>(cs.x), static_cast<float>(cs.y));
+    tab32[d * kRopePairs + (pr ^ (2 * (d & 31)))] = make_float2(static_cast<float>(cs.x), static_cast<float>(cs.y));
   });
   s_depth[tid] = static_cast<uint8_t>(tdepth);
   static_assert(kAttnThreads >= ENTMTP_T_MAX, "one thread per node");
@@ -1060,9 +690,9 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
   stage_barrier();
   if (!qlive) mlo = mhi = u32x4{~0u, ~0u, ~0u, ~0u};   // padding rows see every key
   if (rope) {
-    const float2* tr = tab32 + qdepth * kRopePairs + 8 * lh;
+    const float2* tr = tab32 + qdepth * kRopePairs;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) rope_pairs_f32(qf[s], qf[s + 4], tr + 16 * s);
+    for (int s = 0; s < 4; ++s) rope_pairs_f32(qf[s], qf[s + 4], tr, 16 * s + 8 * lh, 2 * (qdepth & 31));
   }
 
   // l_run: the sum of this lane's half of the keys (the halves meet at the end)
@@ -1091,7 +721,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
       sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(kf), as_bf16x8(qf[s]), sacc, 0, 0, 0);
     }
   };
-  // block i's softmax (lazily raised max, as in tree_attn_kernel) and
+  // block i's softmax (lazily raised max) and
   // O^T += V^T P^T from its slot; prefix: every key of the block is visible
   auto attend = [&](int i, const uint8_t* slot, f32x16& sacc, auto prefix) {
     float bmax = -INFINITY;
@@ -1213,7 +843,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
   if (nb > np) {
     __syncthreads();
     if (rope) {
-      rope_table(sq.D, L, freq, [&](int d, int pr, double2 cs) { tab64(d)[pr] = cs; });
+      rope_table(sq.D, L, freq, [&](int d, int pr, double2 cs) { tab64(d)[pr ^ ((pr >> 3) & 7)] = cs; });
       __syncthreads();
     }
     tree_stage(slot0, tregs, np);
@@ -1237,41 +867,40 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
     }
   }
 
-  // this wave's tile: the output (one split) or its partial
+  // this wave's tile: the output (one split) or its partial.  Lane (query li,
+  // half lh) holds dims 32 ct + 8 j + 4 lh + i in o[ct][4 j + i]; the halves
+  // trade a chunk so that each stores 16 bytes: lane 0..31 dims 8 j .. 8 j + 7
+  // of even j, lane 32..63 of odd j.
   if (!live) return;
   l_run += __shfl_xor(l_run, 32, 64);
   const int row = qt * kQTile + li;
-  if (row >= GT) return;
+  uint16_t* dst;
   if (nsplit == 1) {
-    const int gh = row / T, node = row % T;
-    uint16_t* dst = p.out + (static_cast<size_t>(sq.row0 + node) * p.Hq + g * p.G + gh) * HD;
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        uint2 pk;
-        pk.x = f32_to_bf16_rne(o[ct][4 * j] / l_run) | (f32_to_bf16_rne(o[ct][4 * j + 1] / l_run) << 16);
-        pk.y = f32_to_bf16_rne(o[ct][4 * j + 2] / l_run) | (f32_to_bf16_rne(o[ct][4 * j + 3] / l_run) << 16);
-        *reinterpret_cast<uint2*>(dst + 32 * ct + 8 * j + 4 * lh) = pk;
-      }
+    const int r = row < GT ? row : 0;
+    dst = p.out + (static_cast<size_t>(sq.row0 + r % T) * p.Hq + g * p.G + r / T) * HD;
   } else {
     const size_t prow = sq.part_off + (static_cast<size_t>(split) * p.Hkv + g) * rows_pad + row;
-    uint16_t* dst = p.part_o + prow * HD;
-    const float il = l_run > 0.f ? 1.f / l_run : 0.f;   // 0: no key of the split is visible
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        uint2 pk;
-        pk.x = f32_to_bf16_rne(o[ct][4 * j] * il) | (f32_to_bf16_rne(o[ct][4 * j + 1] * il) << 16);
-        pk.y = f32_to_bf16_rne(o[ct][4 * j + 2] * il) | (f32_to_bf16_rne(o[ct][4 * j + 3] * il) << 16);
-        *reinterpret_cast<uint2*>(dst + 32 * ct + 8 * j + 4 * lh) = pk;
-      }
-    if (lh == 0) {
+    dst = p.part_o + prow * HD;
+    if (lh == 0 && row < GT) {
       p.part_ml[prow * 2 + 0] = m_run;
       p.part_ml[prow * 2 + 1] = l_run;
     }
   }
+  const float il = l_run > 0.f ? 1.f / l_run : 0.f;   // 0: no key of the split is visible
+  auto pack = [&](float x, float y) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x * il, y * il}), bf16x2));
+  };
+#pragma unroll
+  for (int ct = 0; ct < 4; ++ct)
+#pragma unroll
+    for (int j = 0; j < 4; j += 2) {
+      const f32x16& a = o[ct];
+      const auto x = __builtin_amdgcn_permlane32_swap(pack(a[4 * j], a[4 * j + 1]),
+                                                      pack(a[4 * j + 4], a[4 * j + 5]), false, false);
+      const auto y = __builtin_amdgcn_permlane32_swap(pack(a[4 * j + 2], a[4 * j + 3]),
+                                                      pack(a[4 * j + 6], a[4 * j + 7]), false, false);
+      if (row < GT) *reinterpret_cast<u32x4*>(dst + 32 * ct + 8 * (j + lh)) = u32x4{x[0], y[0], x[1], y[1]};
+    }
 }
 
 // ----------------------------------------------------------------- merge --
@@ -1283,15 +912,13 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_q4_kernel(BatchArgs
 // rounds), the group reduces the (max, sum) pairs to the common max and the
 // normalised split weights, and combines; splits past the batch follow four
 // at a time.
-constexpr int kMergeRows = 8;
 constexpr int kMergeBatch = 16;   // splits whose partials are requested together
 constexpr int kMergeThreads = 32 * kMergeRows;
 static_assert(kMaxSplits <= 32, "a half-wavefront holds one lane per split");
 
 template <bool DEVB>
 __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(BatchArgs p) {
-  const int b = seq_of(p, static_cast<int>(blockIdx.x), [](const SeqPlan& q) { return q.merge0; });
-  const SeqPlan sq = DEVB ? resolve_batch(p, b) : resolve(p, b);
+  const SeqPlan sq = plan_of<DEVB, true>(p, static_cast<int>(blockIdx.x));
   if (sq.nsplit == 1 || sq.T == 0) return;   // written by the attend kernel, or nothing to do
   const int GT = p.G * sq.T;
   const int local = (blockIdx.x - sq.merge0) * kMergeRows + (threadIdx.x >> 5);
@@ -1353,17 +980,10 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(BatchArgs p) 
 
 size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// lds: bytes of the one-tile kernel's rotation table (rope_lds_bytes of the
-// deepest tree)
 template <bool DEVB = false>
-void launch_attend(const BatchArgs& a, int items, size_t lds, hipStream_t s) {
-  if (a.nt == 4)
-    hipLaunchKernelGGL(tree_attn_q4_kernel<DEVB>, dim3(items), dim3(kAttnThreads), 0, s, a);
-  else
-    hipLaunchKernelGGL(tree_attn_kernel<DEVB>, dim3(items), dim3(kAttnThreads), lds, s, a);
+void launch_attend(const BatchArgs& a, int items, hipStream_t s) {
+  hipLaunchKernelGGL(tree_attn_kernel<DEVB>, dim3(items), dim3(kAttnThreads), 0, s, a);
 }
-
-
 
 int device_cus() {
   static int cus[64] = {0};
@@ -1380,16 +1000,26 @@ int device_cus() {
 // Grid sizes of one call.
 struct CallShape {
   int rows = 0;          // concatenated tree rows
-  int D = 0;             // depth of the deepest tree
   int items = 0;         // attend workgroups
   int merge_blocks = 0;  // merge blocks
   size_t need = 0;       // workspace bytes
 };
 
+int bank_rows(const entmtp_bank* bank) {   // nodes of the largest tree
+  int T = 0;
+  for (const TopoDesc& td : bank->desc) T = td.T > T ? td.T : T;
+  return T;
+}
+
+// Streams a batch can have at most, whatever trees of at most `rows` rows
+// together it names: a sequence's query groups number at most G T / 128 + 1.
+long long streams_bound(int B, int Hkv, int G, long long rows) {
+  return Hkv * (rows * G / (kTilesPerWg * kQTile) + B);
+}
+
 // Plans the sequences of one call: per-sequence split counts (a lone
 // sequence fills the CUs by itself; a batch shares one blocks-per-split
-// target sized to about kBatchWgPerCu workgroups per CU), grid ranges and the packed
-// workspace layout (output partials, then (max, sum) partials).
+// target, batch_cost), grid ranges and the packed workspace layout (output partials, then (max, sum) partials).
 CallShape plan_call(const entmtp_bank* bank, int B, const int32_t* topo, const int32_t* L,
                     entmtp_bf16* const* kc, entmtp_bf16* const* vc, int cap, int Hq, int Hkv,
                     BatchArgs& a) {
@@ -1406,19 +1036,38 @@ CallShape plan_call(const entmtp_bank* bank, int B, const int32_t* topo, const i
   a.cap = cap;
   const int cus = device_cus();
   a.cus = cus;
-  a.nt = 1;   // the largest tile count any sequence needs
-  for (int b = 0; b < B; ++b) {
-    const int nt = tree_tiles(a.G, bank->desc[topo[b]].T);
-    a.nt = nt > a.nt ? nt : a.nt;
+  const int slots = cus * kWgPerCu;
+  int target = 1;   // blocks per split (a batch of several)
+  if (B > 1) {
+    int nb[kMaxSeqs], H[kMaxSeqs], nb_max = 0;
+    long long work = 0;   // key-block streams
+    for (int b = 0; b < B; ++b) {
+      const int T = bank->desc[topo[b]].T;
+      H[b] = Hkv * query_groups(rows_padded(a.G, T) / kQTile);
+      nb[b] = (L[b] + T + KB - 1) / KB;
+      nb_max = nb[b] > nb_max ? nb[b] : nb_max;
+      work += static_cast<long long>(H[b]) * nb[b];
+    }
+    // (by the bank, not the trees named: a device-planned batch decides alike)
+    const bool two = two_rounds(streams_bound(B, Hkv, a.G, static_cast<long long>(B) * bank_rows(bank)), slots);
+    unsigned long long best = ~0ull;
+    for (int k = 0; k < kTargets; ++k) {
+      if (target_sixteenths(k) < 16 && !two) continue;
+      const int t = batch_target(k, work, nb_max, slots);
+      long long items = 0;
+      bool split = false;
+      for (int b = 0; b < B; ++b) {
+        const int n = batch_splits(nb[b], t);
+        items += static_cast<long long>(H[b]) * n;
+        split = split || n > 1;
+      }
+      const unsigned long long cost = batch_cost(k, t, items, split, slots);
+      if (cost < best) {
+        best = cost;
+        target = t;
+      }
+    }
   }
-  long long work = 0;   // key-block streams
-  for (int b = 0; b < B; ++b) {
-    const int T = bank->desc[topo[b]].T;
-    const int nqg = query_groups(rows_padded(a.G, T) / kQTile, a.nt);
-    work += static_cast<long long>(Hkv) * nqg * ((L[b] + T + KB - 1) / KB);
-  }
-  const long long per_wg = (work + kBatchWgPerCu * cus - 1) / (kBatchWgPerCu * cus);
-  const int target_bps = static_cast<int>(per_wg > kMinBlocksPerSplit ? per_wg : kMinBlocksPerSplit);
 
   CallShape sh;
   long long part_rows = 0;
@@ -1435,24 +1084,13 @@ CallShape plan_call(const entmtp_bank* bank, int B, const int32_t* topo, const i
     q.row0 = sh.rows;
     q.rows_pad = rows_padded(a.G, q.T);
     q.nqt = q.rows_pad / kQTile;
-    q.nqg = query_groups(q.nqt, a.nt);
-    q.nt = a.nt;
+    q.nqg = query_groups(q.nqt);
     const int nblocks = (q.L + q.T + KB - 1) / KB;
-    int ns;
-    if (B == 1) {
-      ns = split_single(nblocks, Hkv * q.nqg, cus * wg_per_cu(a.nt));
-    } else {
-      ns = (nblocks + target_bps - 1) / target_bps;
-      const int bound = split_bound(nblocks);
-      ns = ns < 1 ? 1 : (ns > bound ? bound : ns);
-    }
-    q.bps = (nblocks + ns - 1) / ns;
-    q.nsplit = (nblocks + q.bps - 1) / q.bps;
+    q.nsplit = B == 1 ? split_single(nblocks, Hkv * q.nqg, cus) : batch_splits(nblocks, target);
     q.item0 = sh.items;
     q.merge0 = sh.merge_blocks;
     q.part_off = part_rows;
     sh.rows += q.T;
-    sh.D = q.D > sh.D ? q.D : sh.D;
     sh.items += (Hkv * q.nsplit + 7) / 8 * 8 * q.nqg;
     if (q.nsplit > 1) {
       sh.merge_blocks += (Hkv * a.G * q.T + kMergeRows - 1) / kMergeRows;
@@ -1475,7 +1113,7 @@ int32_t launch_call(BatchArgs& a, const CallShape& sh, void* workspace, hipStrea
   const size_t po = static_cast<size_t>(part_rows) * HD * sizeof(uint16_t);
   a.part_o = reinterpret_cast<uint16_t*>(ws);
   a.part_ml = reinterpret_cast<float*>(ws + al256(po));
-  launch_attend(a, sh.items, rope_lds_bytes(sh.D, a.theta), s);
+  launch_attend(a, sh.items, s);
   if (int32_t rc = launch_status("tree_attn launch")) return rc;
   if (sh.merge_blocks > 0) {
     hipLaunchKernelGGL(attn_merge_kernel<false>, dim3(sh.merge_blocks), dim3(kMergeThreads), 0, s, a);
@@ -1535,16 +1173,12 @@ int32_t attn_device_shape(const entmtp_bank* bank, int Hq, int Hkv, int cap, Dev
   DevAttnShape sh;
   for (const TopoDesc& td : bank->desc) {
     sh.T_max = td.T > sh.T_max ? td.T : sh.T_max;
-    sh.D_max = td.D > sh.D_max ? td.D : sh.D_max;
-    const int nt = tree_tiles(G, td.T);
-    const int nqg = query_groups(rows_padded(G, td.T) / kQTile, nt);
+    const int nqg = query_groups(rows_padded(G, td.T) / kQTile);
     const int max_blocks = (cap + KB - 1) / KB;
     for (int nblocks = 1; nblocks <= max_blocks; ++nblocks) {
-      const int ns0 = split_single(nblocks, Hkv * nqg, cus * wg_per_cu(nt));
-      const int bps = (nblocks + ns0 - 1) / ns0;
-      const int ns = (nblocks + bps - 1) / bps;
+      const int ns = split_single(nblocks, Hkv * nqg, cus);
       const int items = (Hkv * ns + 7) / 8 * 8 * nqg;
-      sh.items[nt] = items > sh.items[nt] ? items : sh.items[nt];
+      sh.items = items > sh.items ? items : sh.items;
     }
   }
   sh.rows = sh.T_max;
@@ -1558,11 +1192,10 @@ void attn_device_splits(const entmtp_bank* bank, int Hq, int Hkv, DevTopo* topos
   const int cus = device_cus();
   const int G = Hq / Hkv;
   for (size_t k = 0; k < bank->desc.size(); ++k) {
-    const int nt = tree_tiles(G, bank->desc[k].T);
-    const int nqg = query_groups(rows_padded(G, bank->desc[k].T) / kQTile, nt);
+    const int nqg = query_groups(rows_padded(G, bank->desc[k].T) / kQTile);
     topos[k].splits[0] = 1;
     for (int b = 1; b <= kMaxSplits; ++b)
-      topos[k].splits[b] = static_cast<unsigned char>(split_for_bound(b, Hkv * nqg, cus * wg_per_cu(nt)));
+      topos[k].splits[b] = static_cast<unsigned char>(split_for_bound(b, Hkv * nqg, cus * kWgPerCu));
   }
 }
 
@@ -1596,50 +1229,48 @@ int32_t launch_attn_device(const entmtp_bank* bank, const DevStep* dev, const De
   uint8_t* ws = static_cast<uint8_t*>(workspace);
   a.part_o = reinterpret_cast<uint16_t*>(ws);
   a.part_ml = reinterpret_cast<float*>(ws + al256(po));
-  // one instance per tile count among the bank's trees; those not made for
-  // the device's tree leave at once
-  for (int nt = 1; nt <= 4; nt *= 2) {
-    if (sh.items[nt] == 0) continue;
-    a.nt = nt;
-    launch_attend(a, sh.items[nt], rope_lds_bytes(sh.D_max, a.theta), s);
-    if (int32_t rc = launch_status("tree_attn launch")) return rc;
-  }
+  launch_attend(a, sh.items, s);
+  if (int32_t rc = launch_status("tree_attn launch")) return rc;
   hipLaunchKernelGGL(attn_merge_kernel<false>, dim3(sh.merge_blocks), dim3(kMergeThreads), 0, s, a);
   return launch_status("tree_attn merge launch");
 }
 
-// Fixed per-sequence ranges of a device-planned batch: each sequence slot
-// gets the grid, merge blocks and partial rows of the largest plan any bank
-// tree can need at prefix lengths up to cap - T, for either tile count.
+// What the host fixes of a device-planned batch: grids that cover every plan
+// the device can make, and per-sequence partial ranges sized for the largest
+// plan any bank tree can need at prefix lengths up to cap - T.
 struct BatchDevShape {
-  int items[5] = {0, 0, 0, 0, 0};   // attend workgroups per sequence, instance with 1 / 4 tiles
-  int merge_blocks = 0;             // merge blocks per sequence
-  long long part_rows = 0;          // partial rows per sequence
-  int D_max = 0;
-  size_t need = 0;                  // workspace bytes for B sequences
+  int items = 0;             // attend workgroups
+  int merge_blocks = 0;
+  bool two = false;          // two-round candidates allowed (two_rounds)
+  long long part_rows = 0;   // partial rows per sequence
+  size_t need = 0;           // workspace bytes for B sequences
 };
 
-BatchDevShape batch_dev_shape(const entmtp_bank* bank, int B, int Hq, int Hkv, int cap) {
+BatchDevShape batch_dev_shape(const entmtp_bank* bank, int B, int Hq, int Hkv, int cap, int rows_cap) {
   BatchDevShape sh;
   const int G = Hq / Hkv;
+  const int slots = device_cus() * kWgPerCu;
   const int bound = split_bound((cap + KB - 1) / KB);
-  int T_max = 0;
-  bool any_small = false;
-  for (const TopoDesc& td : bank->desc) {
-    T_max = td.T > T_max ? td.T : T_max;
-    sh.D_max = td.D > sh.D_max ? td.D : sh.D_max;
-    any_small = any_small || tree_tiles(G, td.T) == 1;
-    // the four-tile instance serves every tree (a batch takes its largest
-    // tile count); the one-tile instance only batches of small trees
-    const int nqt = rows_padded(G, td.T) / kQTile;
-    const int items4 = (Hkv * bound + 7) / 8 * 8 * query_groups(nqt, 4);
-    sh.items[4] = items4 > sh.items[4] ? items4 : sh.items[4];
-  }
-  if (any_small) sh.items[1] = (Hkv * bound + 7) / 8 * 8;
-  sh.merge_blocks = (Hkv * G * T_max + kMergeRows - 1) / kMergeRows;
+  const int T_max = bank_rows(bank);
+  sh.two = two_rounds(streams_bound(B, Hkv, G, static_cast<long long>(B) * T_max), slots);
+  // tree rows of the batch (the sequences' rows are disjoint and within rows_cap)
+  const long long rows = std::min<long long>(rows_cap, static_cast<long long>(B) * T_max);
+  const long long streams = streams_bound(B, Hkv, G, rows);
+  // items of a batch: at most work / t + streams (t at least half the even
+  // share with two rounds, else the whole of it), or every sequence at its
+  // bound; the padding of a (KV head, split) range to eight adds up to seven
+  // workgroups per query group
+  const long long groups = rows * G / (kTilesPerWg * kQTile) + B;
+  const int nqg = query_groups(rows_padded(G, T_max) / kQTile);
+  const long long most = B == 1 ? static_cast<long long>(Hkv) * bound * nqg
+                                : (sh.two ? 2LL : 1LL) * slots + streams;
+  const long long all = static_cast<long long>(B) * ((Hkv * bound + 7) / 8 * 8) * nqg;
+  sh.items = static_cast<int>(std::min(most + 7 * groups, all));
+  // merge blocks: a row of Hq heads per tree row, kMergeRows to a block
+  sh.merge_blocks = static_cast<int>(rows * Hq / kMergeRows + B);
   sh.part_rows = static_cast<long long>(bound) * Hkv * rows_padded(G, T_max);
-  const size_t rows = static_cast<size_t>(B) * sh.part_rows;
-  sh.need = al256(rows * HD * sizeof(uint16_t)) + al256(rows * 2 * 4);
+  const size_t prows = static_cast<size_t>(B) * sh.part_rows;
+  sh.need = al256(prows * HD * sizeof(uint16_t)) + al256(prows * 2 * 4);
   return sh;
 }
 
@@ -1787,7 +1418,7 @@ extern "C" size_t entmtp_tree_attn_batched_device_workspace(const entmtp_bank* b
   if (!bank || bank->desc.empty() || B < 1 || B > ENTMTP_B_MAX || Hq < 1 || Hkv < 1 ||
       Hq % Hkv || d != HD || cap < 1)
     return 0;
-  return batch_dev_shape(bank, B, Hq, Hkv, cap).need;
+  return batch_dev_shape(bank, B, Hq, Hkv, cap, 1).need;   // (not a matter of the rows)
 }
 
 extern "C" int32_t entmtp_tree_attn_batched_device(
@@ -1814,7 +1445,7 @@ extern "C" int32_t entmtp_tree_attn_batched_device(
                      ENTMTP_EINVAL, "sequence %d: caches must be non-NULL and 16-byte aligned", b);
   if (int32_t rc = check_common(Hq, Hkv, d, scale, rope_theta, q, k_tree, v_tree, out, workspace))
     return rc;
-  const BatchDevShape sh = batch_dev_shape(bank, B, Hq, Hkv, cap);
+  const BatchDevShape sh = batch_dev_shape(bank, B, Hq, Hkv, cap, rows_cap);
   ENTMTP_CHECK_ARG(ws_bytes >= sh.need, ENTMTP_ENOSPC, "workspace has %zu bytes, needs %zu",
                    ws_bytes, sh.need);
   BatchArgs a{};
@@ -1849,18 +1480,12 @@ extern "C" int32_t entmtp_tree_attn_batched_device(
   for (int b = 0; b < B; ++b) {
     a.s[b].kc = k_caches[b];
     a.s[b].vc = v_caches[b];
-    a.s[b].merge0 = b * sh.merge_blocks;
     a.s[b].part_off = b * sh.part_rows;
   }
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  // one instance per tile count; a batch's workgroups in the other leave at once
-  for (int nt = 1; nt <= 4; nt *= 4) {
-    if (sh.items[nt] == 0) continue;
-    a.nt = nt;
-    for (int b = 0; b < B; ++b) a.s[b].item0 = b * sh.items[nt];
-    launch_attend<true>(a, B * sh.items[nt], rope_lds_bytes(sh.D_max, a.theta), s);
-    if (int32_t rc = launch_status("tree_attn (device-planned batch) launch")) return rc;
-  }
-  hipLaunchKernelGGL(attn_merge_kernel<true>, dim3(B * sh.merge_blocks), dim3(kMergeThreads), 0, s, a);
+  a.two_rounds = sh.two;
+  launch_attend<true>(a, sh.items, s);
+  if (int32_t rc = launch_status("tree_attn (device-planned batch) launch")) return rc;
+  hipLaunchKernelGGL(attn_merge_kernel<true>, dim3(sh.merge_blocks), dim3(kMergeThreads), 0, s, a);
   return launch_status("tree_attn (device-planned batch) merge launch");
 }
