@@ -50,6 +50,11 @@ __device__ __forceinline__ void buf_dma16(__amdgpu_buffer_rsrc_t buf, uint32_t v
   __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (lds_void*)lds, 16, voff, 0, 0, 0);
 }
 
+// Four bytes at byte voff + soff of the buffer (zero past its end).
+__device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t buf, uint32_t voff, int soff) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(buf, static_cast<int>(voff), soff, 0));
+}
+
 // Workgroup barrier without a memory-model fence.  __syncthreads() would add
 // a release fence, which waits for every outstanding load (the LDS-DMA
 // stages count as LDS writes) and so drains the pipeline; here the waits are
