@@ -840,7 +840,7 @@ bool launch_hyb_dispatch(const uint16_t* X, const uint16_t* W, float* logits, in
   // (96 -> 106 us)
   // many rows: the tiled contraction reads W once per 128 rows with each
   // LDS byte feeding more products
-  if (lm_gemm_takes(T, hid, hyb_grid(V), device_cus())) {
+  if (lm_gemm_takes(T, hid, V, hyb_grid(V), device_cus())) {
     if (ev0)
       if ((*rc = hip_status(hipEventRecord(ev0, s), "hipEventRecord"))) return true;
     *rc = launch_lm_gemm(reinterpret_cast<const entmtp_bf16*>(X),

@@ -33,7 +33,7 @@
 //    block into one partial (the streaming kernels' layout: the block's
 //    partial in its first slice, neutral partials in the other three), so
 //    the statistics merge is unchanged.
-// Hidden sizes 4096 and 5120 (the stage count is a template parameter).
+// Hidden sizes: multiples of 512 (those of the streaming kernels' partials).
 #include <type_traits>
 
 #include "common.hpp"
@@ -42,6 +42,9 @@
 
 namespace entmtp {
 namespace {
+
+// four floats at any address a float may have (one 16-byte store all the same)
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kGemmBN = 128;        // rows of X per pass
 constexpr int kGemmBK = 64;         // k per stage: two MFMA k-steps, 128-byte rows
@@ -117,6 +120,7 @@ __device__ __forceinline__ void gemm_tile(
     uint8_t* __restrict__ ring, const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
     float* __restrict__ logits, int T, int hid, int V, int G, float inv_temp,
     StatPart* __restrict__ part, int grp, int j0, int r0, int r1) {
+  const int nst = NST > 0 ? NST : hid / kGemmBK;   // stages
   using Sh = GemmShape<BM, BN, NW>;
   constexpr int kSlices = Sh::SLICES;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -148,14 +152,14 @@ __device__ __forceinline__ void gemm_tile(
   };
   // blocks walk K in rotated order, so that CUs do not all stream the same
   // column band of W at once
-  const int rot = static_cast<int>((static_cast<unsigned>(grp) * 7u) % static_cast<unsigned>(NST));
+  const int rot = static_cast<int>((static_cast<unsigned>(grp) * 7u) % static_cast<unsigned>(nst));
   const uint8_t* const Wb = reinterpret_cast<const uint8_t*>(W);
   const uint8_t* const Xb = reinterpret_cast<const uint8_t*>(X);
   u32x4 pre[kGemmD][Sh::LI];
   // load q of stage `stage` (clamped to the last stage)
   auto load_one = [&](u32x4& r, int q, int stage) {
-    int ks = (stage < NST ? stage : NST - 1) + rot;
-    ks = ks >= NST ? ks - NST : ks;
+    int ks = (stage < nst ? stage : nst - 1) + rot;
+    ks = ks >= nst ? ks - nst : ks;
     const uint32_t off = src[q] + static_cast<uint32_t>(ks * Sh::ROWB);
     // W is streamed once: keep it out of the caches' way; X is re-read
     if (q < Sh::AI)
@@ -297,8 +301,8 @@ __device__ __forceinline__ void gemm_tile(
   using I3 = std::integral_constant<int, 3>;
   using I4 = std::integral_constant<int, 4>;
   using I5 = std::integral_constant<int, 5>;
-  constexpr int kRounds = NST / 6;
-  for (int c = 0; c < 6 * kRounds; c += 6) {
+  int c = 0;
+  for (; c + 6 <= nst; c += 6) {
     step(I0{}, c);
     step(I1{}, c + 1);
     step(I2{}, c + 2);
@@ -306,18 +310,16 @@ __device__ __forceinline__ void gemm_tile(
     step(I4{}, c + 4);
     step(I5{}, c + 5);
   }
-  constexpr int kTail = NST - 6 * kRounds;
-  if constexpr (kTail > 0) step(I0{}, 6 * kRounds);
-  if constexpr (kTail > 1) step(I1{}, 6 * kRounds + 1);
-  if constexpr (kTail > 2) step(I2{}, 6 * kRounds + 2);
-  if constexpr (kTail > 3) step(I3{}, 6 * kRounds + 3);
-  if constexpr (kTail > 4) step(I4{}, 6 * kRounds + 4);
+  if (c < nst) step(I0{}, c);
+  if (c + 1 < nst) step(I1{}, c + 1);
+  if (c + 2 < nst) step(I2{}, c + 2);
+  if (c + 3 < nst) step(I3{}, c + 3);
+  if (c + 4 < nst) step(I4{}, c + 4);
   mfma_drain();
   pin_acc();
 
   const int vbase = r0 + wm * Sh::WM + 4 * lg;   // first of the lane's rows in block mi = 0
   if (logits) {
-    const bool vec_ok = (V & 3) == 0;
 #pragma unroll
     for (int mi = 0; mi < Sh::MI; ++mi) {
       const int v = vbase + 16 * mi;
@@ -329,8 +331,8 @@ __device__ __forceinline__ void gemm_tile(
         const int node = j0 + wn * Sh::WN + 16 * ni + lr;
         if (node >= T) continue;
         float* dst = logits + static_cast<size_t>(node) * V + v;
-        if (vec_ok && v + 3 < r1) {
-          *reinterpret_cast<f32x4*>(dst) = acc[mi][ni];
+        if (v + 3 < r1) {   // (a row of an odd V starts at any multiple of four bytes)
+          *reinterpret_cast<f32x4_any*>(dst) = acc[mi][ni];
         } else {
 #pragma unroll
           for (int r = 0; r < 4; ++r)
@@ -472,20 +474,13 @@ int32_t launch_gemm(const uint16_t* X, const uint16_t* W, float* logits, int T, 
 // than four (2 x 2) at 90-544 rows.
 constexpr int kWideWaves = 8;
 
-template <int NST>
-int32_t launch_gemm_bm(bool wide, const uint16_t* X, const uint16_t* W, float* logits, int T,
-                       int hid, int V, int G, float inv_temp, StatPart* part, hipStream_t s) {
-  if (wide)
-    return part ? launch_gemm<256, kWideWaves, NST, true>(X, W, logits, T, hid, V, G, inv_temp, part, s)
-                : launch_gemm<256, kWideWaves, NST, false>(X, W, logits, T, hid, V, G, inv_temp, nullptr, s);
-  return part ? launch_gemm<128, 4, NST, true>(X, W, logits, T, hid, V, G, inv_temp, part, s)
-              : launch_gemm<128, 4, NST, false>(X, W, logits, T, hid, V, G, inv_temp, nullptr, s);
-}
-
 }  // namespace
 
-bool lm_gemm_takes(int T, int hid, int G, int cus) {
-  if ((hid != 64 * kGemmBK && hid != 80 * kGemmBK) || G % 4 != 0) return false;
+bool lm_gemm_takes(int T, int hid, int V, int G, int cus) {
+  // (the tile addresses W and X by 32-bit byte offsets)
+  if (hid % 512 || G % 4 != 0 || static_cast<uint64_t>(V) * hid * 2 > UINT32_MAX ||
+      static_cast<uint64_t>(T) * hid * 2 > UINT32_MAX)
+    return false;
   // more than one streaming pass of 128 rows, or more than 64 rows and a
   // block per CU
   return T > kGemmMinRows || (T > kGemmMinRows / 2 && G / 2 >= cus);
@@ -497,9 +492,18 @@ int32_t launch_lm_gemm(const entmtp_bf16* hidden, const entmtp_bf16* w_lm, float
   const auto* X = reinterpret_cast<const uint16_t*>(hidden);
   const auto* W = reinterpret_cast<const uint16_t*>(w_lm);
   auto* part = static_cast<StatPart*>(partials);
-  const bool wide = G / 4 >= cus;   // 256-row blocks still give every CU one
-  if (hid == 64 * kGemmBK) return launch_gemm_bm<64>(wide, X, W, logits, T, hid, V, G, inv_temp, part, s);
-  return launch_gemm_bm<80>(wide, X, W, logits, T, hid, V, G, inv_temp, part, s);
+  auto go = [&](auto nst) {
+    constexpr int NST = decltype(nst)::value;
+    if (G / 4 >= cus)   // 256-row blocks still give every CU one
+      return part ? launch_gemm<256, kWideWaves, NST, true>(X, W, logits, T, hid, V, G, inv_temp, part, s)
+                  : launch_gemm<256, kWideWaves, NST, false>(X, W, logits, T, hid, V, G, inv_temp, nullptr, s);
+    return part ? launch_gemm<128, 4, NST, true>(X, W, logits, T, hid, V, G, inv_temp, part, s)
+                : launch_gemm<128, 4, NST, false>(X, W, logits, T, hid, V, G, inv_temp, nullptr, s);
+  };
+  // the 7B hidden size with its stage count known (in a loop of any count the
+  // 256-row tile spills: 1024 rows at a 128256-entry vocabulary 1043 us, not 1025)
+  if (hid == 64 * kGemmBK) return go(std::integral_constant<int, 64>{});
+  return go(std::integral_constant<int, 0>{});
 }
 
 }  // namespace entmtp
