@@ -458,6 +458,280 @@ __global__ __launch_bounds__(64 * NW) void lm_head_gemm_kernel(
   }
 }
 
+// ---------------------------------------------------------------------------
+// 256 x 256 tiles, for batches that fill 256-row passes.  Four waves (2 x 2,
+// one per SIMD) of 128 x 128 sub-tiles on v_mfma_f32_32x32x16_bf16: a wave
+// reads 8 fragments for 16 products, so the LDS gives 32 KB per 16 k where
+// the 256 x 128 tile's eight waves take 32 KB for half the products, and each
+// pass of W serves twice the rows.  W and X reach LDS by direct buffer copies
+// (8 rows x 128 bytes an instruction, rows past the block or the batch arrive
+// as zeros): no staging registers beside the 256 accumulators.  Stages of 64
+// k: W in a ring of three slots (two stages ahead: it may come from HBM), X in
+// two (one stage ahead: L2), all 160 KB.  One barrier a stage, before its last
+// k-step: by then every wave has that step's fragments in registers, so both
+// the next stage's arrival and the freed slots are announced at once.
+// ---------------------------------------------------------------------------
+constexpr int kBigRows = 256;
+constexpr int kBigSlot = kBigRows * kGemmBK * 2;   // 32 KB
+constexpr int kBigThreads = 256;
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// chunk c of row r lies at position c ^ big_swz(r): any 8 consecutive rows, 8
+// of one parity among 16 and 8 equal mod 4 among 32 fall on distinct positions
+// (each a way the LDS may group a fragment read's lanes)
+__device__ __forceinline__ int big_swz(int r) { return (r ^ ((r & 31) >> 3)) & 7; }
+
+template <bool STATS>
+__global__ __launch_bounds__(kBigThreads, 1) void lm_head_gemm256_kernel(
+    const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, float* __restrict__ logits,
+    int T, int hid, int V, int G, float inv_temp, StatPart* __restrict__ part) {
+  // one LDS object per slot (the compiler then knows that reads of one do not
+  // wait for copies into another)
+  __shared__ __attribute__((aligned(16))) uint8_t w0[kBigSlot];
+  __shared__ __attribute__((aligned(16))) uint8_t w1[kBigSlot];
+  __shared__ __attribute__((aligned(16))) uint8_t w2[kBigSlot];
+  __shared__ __attribute__((aligned(16))) uint8_t x0[kBigSlot];
+  __shared__ __attribute__((aligned(16))) uint8_t x1[kBigSlot];
+  uint8_t* const wring[3] = {w0, w1, w2};
+  uint8_t* const xring[2] = {x0, x1};
+  constexpr int kSlices = kBigRows / 64;
+  const int groups = (G + kSlices - 1) / kSlices;
+  const int passes = (T + kBigRows - 1) / kBigRows;
+  const int bid = blockIdx.x, r8 = bid >> 3;
+  const int pass = r8 % passes, grp = (r8 / passes) * 8 + (bid & 7);
+  if (grp >= groups) return;
+  const int j0 = pass * kBigRows;
+  const int r0 = slice_begin(kSlices * grp, G, V);
+  const int r1 = slice_begin(kSlices * grp + kSlices, G, V);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int li = lane & 31, lh = lane >> 5;
+  const int wm = wave & 1, wn = wave >> 1;
+  const StatPart empty{-INFINITY, 0.f, 0.f, 0x7fffffff};
+  if (r0 >= r1) {   // empty block (tiny V): neutral partials only
+    if constexpr (STATS)
+      if (j0 + tid < T)
+        for (int u = 0; u < kSlices && kSlices * grp + u < G; ++u)
+          part[static_cast<size_t>(j0 + tid) * G + kSlices * grp + u] = empty;
+    return;
+  }
+  const int nst = hid / kGemmBK;
+  const int rot = static_cast<int>((static_cast<unsigned>(grp) * 7u) % static_cast<unsigned>(nst));
+  const __amdgpu_buffer_rsrc_t wbuf =
+      dma_buffer(W + static_cast<size_t>(r0) * hid, static_cast<uint32_t>(r1 - r0) * hid * 2u);
+  const __amdgpu_buffer_rsrc_t xbuf =
+      dma_buffer(X + static_cast<size_t>(j0) * hid, static_cast<uint32_t>(min(kBigRows, T - j0)) * hid * 2u);
+  // copy q of a wave fills rows 8 (8 wave + q) .. + 7 of a slot
+  uint32_t voff[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int row = 8 * (8 * wave + q) + (lane >> 3);
+    voff[q] = static_cast<uint32_t>(row) * hid * 2u + (((lane & 7) ^ big_swz(row)) << 4);
+  }
+  auto soff = [&](int stage) {
+    int ks = (stage < nst ? stage : nst - 1) + rot;   // (past the last: that one again, never read)
+    ks = ks >= nst ? ks - nst : ks;
+    return ks * (kGemmBK * 2);
+  };
+  auto copy_w = [&](uint8_t* slot, int q, int so) { buf_dma16_at(wbuf, voff[q], so, slot + (8 * wave + q) * 1024); };
+  auto copy_x = [&](uint8_t* slot, int q, int so) { buf_dma16_at(xbuf, voff[q], so, slot + (8 * wave + q) * 1024); };
+
+  f32x16 acc[4][4];
+#pragma unroll
+  for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < 4; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+  auto pin_acc = [&]() {   // (see gemm_tile)
+#pragma unroll
+    for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < 4; ++ni) asm volatile("" : "+a"(acc[mi][ni]));
+  };
+  // fragment f of k-step j of a stage: W block f (f < 4) or X block f - 4, 32
+  // rows, chunk 2 j + lh
+  bf16x8 frag[2][8];
+  const int arow = (wm * 128 + li) * 128, brow = (wn * 128 + li) * 128;
+  auto read = [&](bf16x8& out, const uint8_t* ws, const uint8_t* xs, int j, int f) {
+    const int pos = ((2 * j + lh) ^ big_swz(li)) << 4;
+    out = as_bf16x8(*reinterpret_cast<const u32x4*>(f < 4 ? ws + arow + f * 4096 + pos
+                                                          : xs + brow + (f - 4) * 4096 + pos));
+  };
+  auto mfma = [&](int set, int i) {
+    const int mi = i >> 2, ni = i & 3;
+    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
+                 : "+a"(acc[mi][ni])
+                 : "v"(frag[set][mi]), "v"(frag[set][4 + ni])
+                 : "memory");
+  };
+  // the products of one k-step, the next one's fragment reads and four of the
+  // copies issued among them
+  auto step = [&](int set, auto reads, auto copies) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      mfma(set, i);
+      if (i < 8) reads(i);
+      else if (i % 2 == 0) copies((i - 8) / 2);
+    }
+  };
+  auto none = [](int) {};
+
+  // prologue: stages 0 and 1, and W of stage 2
+#pragma unroll
+  for (int q = 0; q < 8; ++q) copy_w(w0, q, soff(0));
+#pragma unroll
+  for (int q = 0; q < 8; ++q) copy_x(x0, q, soff(0));
+#pragma unroll
+  for (int q = 0; q < 8; ++q) copy_w(w1, q, soff(1));
+#pragma unroll
+  for (int q = 0; q < 8; ++q) copy_x(x1, q, soff(1));
+#pragma unroll
+  for (int q = 0; q < 8; ++q) copy_w(w2, q, soff(2));
+  pin_acc();
+  mfma_drain();   // the accumulators' zeroing precedes their first product
+  wait_vmcnt<24>();
+  stage_barrier();
+#pragma unroll
+  for (int f = 0; f < 8; ++f) read(frag[0][f], w0, x0, 0, f);
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+    step(j & 1, [&](int f) { read(frag[(j & 1) ^ 1][f], w0, x0, j + 1, f); }, none);
+  wait_vmcnt<8>();
+  stage_barrier();
+  // body s (K = s mod 6): the last k-step of stage s and the first three of
+  // stage s + 1, X of stage s + 2 and W of s + 3 into the slots stage s left
+  auto body = [&](auto kc, int s) {
+    constexpr int K = decltype(kc)::value;
+    uint8_t* const wn_ = wring[(K + 1) % 3];
+    uint8_t* const xn_ = xring[(K + 1) % 2];
+    uint8_t* const wf = wring[K % 3];
+    uint8_t* const xf = xring[K % 2];
+    const int sx = soff(s + 2), sw = soff(s + 3);
+    step(1, [&](int f) { read(frag[0][f], wn_, xn_, 0, f); }, [&](int q) { copy_x(xf, q, sx); });
+    step(0, [&](int f) { read(frag[1][f], wn_, xn_, 1, f); }, [&](int q) { copy_x(xf, 4 + q, sx); });
+    step(1, [&](int f) { read(frag[0][f], wn_, xn_, 2, f); }, [&](int q) { copy_w(wf, q, sw); });
+    step(0, [&](int f) { read(frag[1][f], wn_, xn_, 3, f); }, [&](int q) { copy_w(wf, 4 + q, sw); });
+    wait_vmcnt<8>();   // all but W of stage s + 3; and this wave's fragments are here
+    stage_barrier();
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+  using I4 = std::integral_constant<int, 4>;
+  using I5 = std::integral_constant<int, 5>;
+  int c = 0;
+  for (; c + 6 < nst; c += 6) {
+    body(I0{}, c);
+    body(I1{}, c + 1);
+    body(I2{}, c + 2);
+    body(I3{}, c + 3);
+    body(I4{}, c + 4);
+    body(I5{}, c + 5);
+  }
+  if (c + 1 < nst) body(I0{}, c);
+  if (c + 2 < nst) body(I1{}, c + 1);
+  if (c + 3 < nst) body(I2{}, c + 2);
+  if (c + 4 < nst) body(I3{}, c + 3);
+  if (c + 5 < nst) body(I4{}, c + 4);
+  step(1, none, none);
+  mfma_drain();
+  pin_acc();
+  wait_vmcnt<0>();   // no copy lands in LDS from here on
+
+  // lane (batch row li, half lh) of block (mi, ni) holds vocabulary rows
+  // 8 (r / 4) + 4 lh + r % 4
+  const int vbase = r0 + wm * 128 + 4 * lh;
+  if (logits) {
+#pragma unroll
+    for (int mi = 0; mi < 4; ++mi) {
+      __builtin_amdgcn_sched_barrier(0);   // (one block row at a time, as in gemm_tile)
+#pragma unroll
+      for (int ni = 0; ni < 4; ++ni) {
+        const int node = j0 + wn * 128 + 32 * ni + li;
+        if (node >= T) continue;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int v = vbase + 32 * mi + 8 * u;
+          float* dst = logits + static_cast<size_t>(node) * V + v;
+          if (v + 3 < r1) {
+            *reinterpret_cast<f32x4_any*>(dst) = f32x4_any{acc[mi][ni][4 * u], acc[mi][ni][4 * u + 1],
+                                                           acc[mi][ni][4 * u + 2], acc[mi][ni][4 * u + 3]};
+          } else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              if (v + r < r1) dst[r] = acc[mi][ni][4 * u + r];
+          }
+        }
+      }
+    }
+  }
+  if constexpr (STATS) {
+    // as in gemm_tile: the lane's rows, its other half's, then the two waves
+    constexpr float kLog2e = 1.44269504088896341f, kLn2 = 0.69314718055994531f;
+    const float it2 = inv_temp * kLog2e;
+    // (rows past the block count as -inf: no branches, which spilled)
+    __syncthreads();   // every wave is done with the ring
+    StatPart* wpart = reinterpret_cast<StatPart*>(x0);   // [2][kBigRows]
+#pragma unroll
+    for (int ni = 0; ni < 4; ++ni) {
+      __builtin_amdgcn_sched_barrier(0);   // one column of blocks at a time
+      StatPart p = empty;
+      auto value = [&](int mi, int r) {
+        return vbase + 32 * mi + 8 * (r >> 2) + (r & 3) < r1 ? acc[mi][ni][r] : -INFINITY;
+      };
+#pragma unroll
+      for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float x = value(mi, r);
+          const bool up = x > p.zmax;
+          p.zmax = up ? x : p.zmax;
+          p.idx = up ? vbase + 32 * mi + 8 * (r >> 2) + (r & 3) : p.idx;
+        }
+      take_max(p.zmax, p.idx, __shfl_xor(p.zmax, 32, 64), __shfl_xor(p.idx, 32, 64));
+      if (p.zmax != -INFINITY) {
+        const float my2 = p.zmax * it2;
+        float Z = 0.f, S2 = 0.f;
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float y2 = fmaxf(fmaf(value(mi, r), it2, -my2), -1000.f);   // (2^-1000 is 0)
+            const float e = __builtin_amdgcn_exp2f(y2);
+            Z += e;
+            S2 = fmaf(y2, e, S2);
+          }
+        p.Z = Z;
+        p.S = S2 * kLn2;
+      }
+      p.Z += __shfl_xor(p.Z, 32, 64);
+      p.S += __shfl_xor(p.S, 32, 64);
+      if (lh == 0) wpart[wm * kBigRows + wn * 128 + 32 * ni + li] = p;
+    }
+    __syncthreads();
+    if (j0 + tid < T) {
+      StatPart q = wpart[tid];
+      part_merge(q, wpart[kBigRows + tid], inv_temp);
+      StatPart* dst = part + static_cast<size_t>(j0 + tid) * G + kSlices * grp;
+      dst[0] = q;
+#pragma unroll
+      for (int u = 1; u < kSlices; ++u)
+        if (kSlices * grp + u < G) dst[u] = empty;
+    }
+  }
+}
+
+template <bool STATS>
+int32_t launch_gemm256(const uint16_t* X, const uint16_t* W, float* logits, int T, int hid, int V,
+                       int G, float inv_temp, StatPart* part, hipStream_t s) {
+  const int groups = (G + kBigRows / 64 - 1) / (kBigRows / 64);
+  const int passes = (T + kBigRows - 1) / kBigRows;
+  hipLaunchKernelGGL(lm_head_gemm256_kernel<STATS>, dim3((groups + 7) / 8 * passes * 8), dim3(kBigThreads),
+                     0, s, X, W, logits, T, hid, V, G, inv_temp, part);
+  return launch_status("verify_logits (256-row tiles) launch");
+}
+
 template <int BM, int NW, int NST, bool STATS>
 int32_t launch_gemm(const uint16_t* X, const uint16_t* W, float* logits, int T, int hid, int V,
                     int G, float inv_temp, StatPart* part, hipStream_t s) {
@@ -476,6 +750,17 @@ constexpr int kWideWaves = 8;
 
 }  // namespace
 
+namespace {
+// 256 x 256 tiles: the last pass of 256 rows is more than half full, and the
+// workgroups (one per CU) fill nine tenths of their rounds.
+bool big_tiles(int T, int G, int cus) {
+  if (T <= kGemmMinRows || (T - 1) % kBigRows < kBigRows / 2) return false;
+  const long long wg = static_cast<long long>(G / 4) * ((T + kBigRows - 1) / kBigRows);
+  const long long rounds = (wg + cus - 1) / cus;
+  return 10 * wg >= 9 * rounds * cus;
+}
+}  // namespace
+
 bool lm_gemm_takes(int T, int hid, int V, int G, int cus) {
   // (the tile addresses W and X by 32-bit byte offsets)
   if (hid % 512 || G % 4 != 0 || static_cast<uint64_t>(V) * hid * 2 > UINT32_MAX ||
@@ -492,6 +777,9 @@ int32_t launch_lm_gemm(const entmtp_bf16* hidden, const entmtp_bf16* w_lm, float
   const auto* X = reinterpret_cast<const uint16_t*>(hidden);
   const auto* W = reinterpret_cast<const uint16_t*>(w_lm);
   auto* part = static_cast<StatPart*>(partials);
+  if (big_tiles(T, G, cus))
+    return part ? launch_gemm256<true>(X, W, logits, T, hid, V, G, inv_temp, part, s)
+                : launch_gemm256<false>(X, W, logits, T, hid, V, G, inv_temp, nullptr, s);
   auto go = [&](auto nst) {
     constexpr int NST = decltype(nst)::value;
     if (G / 4 >= cus)   // 256-row blocks still give every CU one

@@ -45,9 +45,12 @@ __device__ __forceinline__ void lds_dma16(const void* src, void* lds) {
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t dma_buffer(const void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00020000);
 }
-__device__ __forceinline__ void buf_dma16(__amdgpu_buffer_rsrc_t buf, uint32_t voff, void* lds) {
+__device__ __forceinline__ void buf_dma16_at(__amdgpu_buffer_rsrc_t buf, uint32_t voff, int soff, void* lds) {
   typedef __attribute__((address_space(3))) void lds_void;
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (lds_void*)lds, 16, voff, 0, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (lds_void*)lds, 16, voff, soff, 0, 0);
+}
+__device__ __forceinline__ void buf_dma16(__amdgpu_buffer_rsrc_t buf, uint32_t voff, void* lds) {
+  buf_dma16_at(buf, voff, 0, lds);
 }
 
 // Four bytes at byte voff + soff of the buffer (zero past its end).
