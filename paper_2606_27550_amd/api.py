@@ -14,6 +14,15 @@ from typing import Sequence
 
 import numpy as np
 
+# torch owns the device memory and streams handed to the library, so the
+# library must resolve to the HIP runtime torch already loaded (the dynamic
+# loader reuses it by soname when torch comes first).
+try:
+    import torch as _torch
+except ImportError:   # host-only use (banks, ladders)
+    _torch = None
+_raw_stream = getattr(getattr(_torch, "_C", None), "_cuda_getCurrentRawStream", None)
+
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libentmtp.so")
 
 OK, EINVAL, ETREE, ERANGE, ENOSPC, EHIP, ETIMEDOUT = 0, -1, -2, -3, -4, -5, -6
@@ -119,13 +128,6 @@ def _load():
     if not os.path.exists(_LIB_PATH):
         raise ImportError(f"{_LIB_PATH} is missing: build it with "
                           "`python -m paper_2606_27550_amd.build`")
-    # torch owns the device memory and streams handed to the library, so the
-    # library must resolve to the HIP runtime torch already loaded (the
-    # dynamic loader reuses it by soname when torch comes first).
-    try:
-        import torch  # noqa: F401
-    except ImportError:
-        pass
     lib = ctypes.CDLL(_LIB_PATH)
     rts = _hip_runtimes()
     if len(rts) > 1:
@@ -160,18 +162,21 @@ def last_error() -> str:
 
 def _p(t):
     """Device pointer of a tensor (None -> NULL)."""
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _np_p(a: np.ndarray):
     return a.ctypes.data_as(ctypes.c_void_p)
 
 
-def _stream(stream):
+def _stream(stream) -> int:
+    """Handle of a stream (None: torch's current one on the current device)."""
     if stream is None:
-        import torch
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+        # the handle itself: a Stream object for it costs several times the lookup
+        if _raw_stream is not None and _torch.cuda.is_initialized():
+            return _raw_stream(_torch._C._cuda_getDevice())
+        stream = _torch.cuda.current_stream()
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 # --------------------------------------------------------------------- bank --
@@ -253,8 +258,12 @@ def _need(cond: bool, msg: str) -> None:
 
 def _dev(t, name, dtype, shape=None, min_numel=None):
     """Host-side check that a tensor is what the kernel will assume."""
-    import torch
-    _need(isinstance(t, torch.Tensor), f"{name} must be a torch tensor")
+    # one test for a tensor that passes: the messages below are built one by
+    # one, and a call checks up to eleven tensors
+    if (isinstance(t, _torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()
+            and (shape is None or t.shape == shape) and (min_numel is None or t.numel() >= min_numel)):
+        return
+    _need(isinstance(t, _torch.Tensor), f"{name} must be a torch tensor")
     _need(t.is_cuda, f"{name} must live on the GPU")
     _need(t.dtype == dtype, f"{name} must be {dtype}, got {t.dtype}")
     _need(t.is_contiguous(), f"{name} must be contiguous")
@@ -778,7 +787,7 @@ class Step:
                        self.entropy.data_ptr(),
                        self.top1p.data_ptr(), self.argmax.data_ptr(), self.accept_len.data_ptr(),
                        self.bonus.data_ptr(), self.best_top1p.data_ptr(), self.path.data_ptr(),
-                       D + 1, None, 0, _stream(stream).value, tau_on, tau_off,
+                       D + 1, None, 0, _stream(stream), tau_on, tau_off,
                        int(bool(device_prefix_fixed)))
         need = int(lib.entmtp_step_workspace(bank.handle, ctypes.byref(c)))
         if need == 0:

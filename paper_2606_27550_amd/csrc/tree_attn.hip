@@ -404,7 +404,13 @@ __device__ __forceinline__ SeqPlan plan_of(const BatchArgs& p, int x) {
 constexpr int kRopePairs = HD / 2;
 inline void set_rope(BatchArgs& a, float rope_theta) {
   a.theta = static_cast<double>(rope_theta);
-  for (int c = 0; c < kRopePairs; ++c) a.freq[c] = a.theta > 0.0 ? std::pow(a.theta, -2.0 * c / HD) : 0.0;
+  // (a model has one base: its 64 powers are kept, per thread, for the next call)
+  thread_local double last_theta = -1.0, freq[kRopePairs];
+  if (a.theta != last_theta) {
+    for (int c = 0; c < kRopePairs; ++c) freq[c] = a.theta > 0.0 ? std::pow(a.theta, -2.0 * c / HD) : 0.0;
+    last_theta = a.theta;
+  }
+  std::copy(freq, freq + kRopePairs, a.freq);
 }
 // sin and cos of x in fp64, 0 <= x < 2^31 (positions times frequencies up to
 // one radian): x less the nearest multiple n of pi/2 (pi/2 as a sum of two
