@@ -593,13 +593,12 @@ __device__ __forceinline__ void hyb_body(uint8_t* xslot0, uint8_t* xslot1, uint8
       for (int off = 16; off <= 32; off <<= 1)
         take_max(p.zmax, p.idx, __shfl_xor(p.zmax, off, 64), __shfl_xor(p.idx, off, 64));
       if (p.zmax != -INFINITY) {
-        const float my = p.zmax * inv_temp;
 #pragma unroll
         for (int t = 0; t < WT; ++t)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             if (live[t] && vt[t] + r < r1) {
-              const float y = acc[t][n][r] * inv_temp - my;
+              const float y = (acc[t][n][r] - p.zmax) * inv_temp;
               const float e = expf(y);
               p.Z += e;
               if (e > 0.f) p.S += y * e;

@@ -11,8 +11,7 @@
 // through LDS, so each LDS byte feeds 64 to 128 products:
 //  * eight waves in a 4 x 2 grid over the 256 x 128 output tile (two per
 //    SIMD, so one issues products while the other waits), each accumulating
-//    a 64 x 64 sub-tile with v_mfma_f32_16x16x32_bf16 (128-row blocks: four
-//    waves, 2 x 2);
+//    a 64 x 64 sub-tile with v_mfma_f32_16x16x32_bf16;
 //  * K advances in stages of 64: each wave loads its share of a stage's W
 //    and X rows into VGPRs (8 rows x 128 bytes per instruction) two stages
 //    ahead of storing them into one of three LDS slots, two stages ahead of
@@ -33,6 +32,8 @@
 //    block into one partial (the streaming kernels' layout: the block's
 //    partial in its first slice, neutral partials in the other three), so
 //    the statistics merge is unchanged.
+// Where 256-row blocks would leave CUs without one, and for batches that fill
+// 256-row passes, square tiles by direct copies take over (below).
 // Hidden sizes: multiples of 512 (those of the streaming kernels' partials).
 #include <type_traits>
 
@@ -53,8 +54,7 @@ constexpr int kGemmSlots = 3;       // LDS stages: multiplied, read, written
 constexpr int kGemmD = 2;           // stages of loads held in VGPRs ahead of their store
 
 // BM vocabulary rows per block: BM / 64 of the streaming grid's slices (at
-// most 64 rows each), 256 when the vocabulary gives every CU a block (128256
-// entries: 501 blocks), else 128 (32000: 250).
+// most 64 rows each).
 // NW waves: NW / 2 along the vocabulary rows, two along the rows of X.
 template <int BM, int BN, int NW>
 struct GemmShape {
@@ -73,11 +73,8 @@ struct GemmShape {
   static constexpr int WM = BM / WMW, WN = BN / 2;   // wave sub-tile
   static constexpr int MI = WM / 16, NI = WN / 16;
   static constexpr int NF = MI + NI;              // fragments per k-step
-  // Accumulators in AGPRs when a wave's 128 x 64 sub-tile needs 128 of them
-  // beside ~220 VGPRs (one wave per SIMD); with two waves per SIMD the
-  // compiler halves the 256-register budget between the two files once
-  // AGPRs are used, so 64 x 64 sub-tiles keep theirs in VGPRs.
-  static constexpr bool ACC_AGPR = NW == 4;
+  // (accumulators in VGPRs: with two waves per SIMD the compiler halves the
+  // 256-register budget between the two files once AGPRs are used)
   static_assert(BN % (NW * RPI) == 0 && AI % 2 == 0 && BI % 2 == 0, "loads split evenly");
   static_assert(kGemmSlots * SLOT <= 160 * 1024, "slots fit in LDS");
 };
@@ -184,7 +181,7 @@ __device__ __forceinline__ void gemm_tile(
 #pragma unroll
     for (int ni = 0; ni < Sh::NI; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
   bf16x8 frag[2][Sh::NF];
-  // The products accumulate in place (AGPRs or VGPRs), as inline assembly:
+  // The products accumulate in place, as inline assembly:
   // with the builtin the compiler renamed the accumulators from one step to
   // the next and spent a move per accumulator register per loop trip
   // undoing it.  The "memory" clobber keeps the step's loads, stores and
@@ -194,16 +191,10 @@ __device__ __forceinline__ void gemm_tile(
   auto mfma_one = [&](int buf, int i) {
     const int mi = i / Sh::NI, ni = i % Sh::NI;
     if (ni >= NA) return;   // an X block wholly past the batch
-    if constexpr (Sh::ACC_AGPR)
-      asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
-                   : "+a"(acc[mi][ni])
-                   : "v"(frag[buf][mi]), "v"(frag[buf][Sh::MI + ni])
-                   : "memory");
-    else
-      asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
-                   : "+v"(acc[mi][ni])
-                   : "v"(frag[buf][mi]), "v"(frag[buf][Sh::MI + ni])
-                   : "memory");
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
+                 : "+v"(acc[mi][ni])
+                 : "v"(frag[buf][mi]), "v"(frag[buf][Sh::MI + ni])
+                 : "memory");
   };
   // An empty assembly statement that takes and returns every accumulator.
   // mfma_drain() orders memory accesses only: without this the compiler may
@@ -216,12 +207,7 @@ __device__ __forceinline__ void gemm_tile(
 #pragma unroll
     for (int mi = 0; mi < Sh::MI; ++mi)
 #pragma unroll
-      for (int ni = 0; ni < Sh::NI; ++ni) {
-        if constexpr (Sh::ACC_AGPR)
-          asm volatile("" : "+a"(acc[mi][ni]));
-        else
-          asm volatile("" : "+v"(acc[mi][ni]));
-      }
+      for (int ni = 0; ni < Sh::NI; ++ni) asm volatile("" : "+v"(acc[mi][ni]));
   };
   // the fragments in the order the products need them: X blocks (every
   // product of the first W block uses one), then W blocks
@@ -347,7 +333,9 @@ __device__ __forceinline__ void gemm_tile(
     // visits its rows in increasing order, so within the lane a strictly
     // larger value is the only update the lowest-index rule needs.  The
     // sums run in base 2 (one hardware exponential per logit): with
-    // y2 = log2(e) (inv_temp z - my), Z = sum 2^y2 and S = ln 2 sum y2 2^y2.
+    // y2 = log2(e) inv_temp (z - zmax), Z = sum 2^y2 and S = ln 2 sum y2 2^y2
+    // (the difference first: z and zmax scaled apart each bring a rounding of
+    // their own size, the same one for the whole row).
     constexpr float kLog2e = 1.44269504088896341f, kLn2 = 0.69314718055994531f;
     const float it2 = inv_temp * kLog2e;
     const bool full = r1 - r0 == BM;   // every row of the block is a vocabulary row
@@ -370,14 +358,13 @@ __device__ __forceinline__ void gemm_tile(
       for (int off = 16; off <= 32; off <<= 1)
         take_max(p.zmax, p.idx, __shfl_xor(p.zmax, off, 64), __shfl_xor(p.idx, off, 64));
       if (p.zmax != -INFINITY) {
-        const float my2 = p.zmax * it2;
         float Z = 0.f, S2 = 0.f;
 #pragma unroll
         for (int mi = 0; mi < Sh::MI; ++mi)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             if (full || vbase + 16 * mi + r < r1) {
-              const float y2 = fmaf(acc[mi][ni][r], it2, -my2);
+              const float y2 = (acc[mi][ni][r] - p.zmax) * it2;
               const float e = __builtin_amdgcn_exp2f(y2);
               Z += e;
               S2 = fmaf(y2, e, S2);
@@ -459,20 +446,26 @@ __global__ __launch_bounds__(64 * NW) void lm_head_gemm_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// 256 x 256 tiles, for batches that fill 256-row passes.  Four waves (2 x 2,
-// one per SIMD) of 128 x 128 sub-tiles on v_mfma_f32_32x32x16_bf16: a wave
+// Square tiles of 64 MB rows.  MB = 4: 256 x 256, for batches that fill 256-row
+// passes; MB = 2: 128 x 128, where the vocabulary gives the CUs no 256-row
+// block each (32000 entries: 250 of 128 rows).  Four waves (2 x 2, one per
+// SIMD) of 32 MB x 32 MB sub-tiles on v_mfma_f32_32x32x16_bf16: at MB = 4 a wave
 // reads 8 fragments for 16 products, so the LDS gives 32 KB per 16 k where
 // the 256 x 128 tile's eight waves take 32 KB for half the products, and each
 // pass of W serves twice the rows.  W and X reach LDS by direct buffer copies
 // (8 rows x 128 bytes an instruction, rows past the block or the batch arrive
-// as zeros): no staging registers beside the 256 accumulators.  Stages of 64
-// k: W in a ring of three slots (two stages ahead: it may come from HBM), X in
-// two (one stage ahead: L2), all 160 KB.  One barrier a stage, before its last
-// k-step: by then every wave has that step's fragments in registers, so both
-// the next stage's arrival and the freed slots are announced at once.
+// as zeros): no staging registers beside the accumulators.  Stages of 64 k in
+// rings of WR and XR slots: 3 and 2 of 32 KB (all 160 KB of LDS; X, an L2 hit,
+// comes one stage ahead) or 4 and 4 of 16 KB.  One barrier a stage, before its
+// last k-step: by then every wave has that step's fragments in registers, so
+// both the next stage's arrival and the freed slots are announced at once.
+// MB = 4, 1024 rows, hid 4096, 128256 entries: 1049 us (256 x 128) -> 914 (1.18
+// PFLOP/s; 754 with no copies at all, 841 with every W stage an L2 hit); 512
+// rows, 5120, 32000: 236 -> 151.  MB = 2 against 128 x 128 through registers: 70
+// rows, 2048, 40000 59.2 -> 56.0; 140 rows, 3584, 32000 78.8 -> 74.9; 128 rows,
+// 5120, 32000 82.0 -> 79.1.  At 128256 entries it loses to 256 x 128 (128 rows
+// 208 -> 221: every block fetches X).
 // ---------------------------------------------------------------------------
-constexpr int kBigRows = 256;
-constexpr int kBigSlot = kBigRows * kGemmBK * 2;   // 32 KB
 constexpr int kBigThreads = 256;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -481,19 +474,26 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // (each a way the LDS may group a fragment read's lanes)
 __device__ __forceinline__ int big_swz(int r) { return (r ^ ((r & 31) >> 3)) & 7; }
 
-template <bool STATS>
-__global__ __launch_bounds__(kBigThreads, 1) void lm_head_gemm256_kernel(
+template <int MB, int WR, int XR, bool STATS>
+__global__ __launch_bounds__(kBigThreads, 1) void lm_head_square_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, float* __restrict__ logits,
     int T, int hid, int V, int G, float inv_temp, StatPart* __restrict__ part) {
+  constexpr int kBigRows = 64 * MB;                  // rows of W and of X per tile
+  constexpr int kBigSlot = kBigRows * kGemmBK * 2;   // bytes
+  constexpr int LI = 2 * MB;                         // copies per wave and operand a stage
+  static_assert((WR == 3 && XR == 2) || (WR == 4 && XR == 4), "the wait counts below");
   // one LDS object per slot (the compiler then knows that reads of one do not
   // wait for copies into another)
   __shared__ __attribute__((aligned(16))) uint8_t w0[kBigSlot];
   __shared__ __attribute__((aligned(16))) uint8_t w1[kBigSlot];
   __shared__ __attribute__((aligned(16))) uint8_t w2[kBigSlot];
+  __shared__ __attribute__((aligned(16))) uint8_t w3[WR > 3 ? kBigSlot : 16];
   __shared__ __attribute__((aligned(16))) uint8_t x0[kBigSlot];
   __shared__ __attribute__((aligned(16))) uint8_t x1[kBigSlot];
-  uint8_t* const wring[3] = {w0, w1, w2};
-  uint8_t* const xring[2] = {x0, x1};
+  __shared__ __attribute__((aligned(16))) uint8_t x2[XR > 2 ? kBigSlot : 16];
+  __shared__ __attribute__((aligned(16))) uint8_t x3[XR > 2 ? kBigSlot : 16];
+  uint8_t* const wring[4] = {w0, w1, w2, WR > 3 ? w3 : w2};   // (unused slots take no LDS)
+  uint8_t* const xring[4] = {x0, x1, XR > 2 ? x2 : x0, XR > 2 ? x3 : x1};
   constexpr int kSlices = kBigRows / 64;
   const int groups = (G + kSlices - 1) / kSlices;
   const int passes = (T + kBigRows - 1) / kBigRows;
@@ -509,7 +509,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_gemm256_kernel(
   const StatPart empty{-INFINITY, 0.f, 0.f, 0x7fffffff};
   if (r0 >= r1) {   // empty block (tiny V): neutral partials only
     if constexpr (STATS)
-      if (j0 + tid < T)
+      if (tid < kBigRows && j0 + tid < T)
         for (int u = 0; u < kSlices && kSlices * grp + u < G; ++u)
           part[static_cast<size_t>(j0 + tid) * G + kSlices * grp + u] = empty;
     return;
@@ -520,11 +520,11 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_gemm256_kernel(
       dma_buffer(W + static_cast<size_t>(r0) * hid, static_cast<uint32_t>(r1 - r0) * hid * 2u);
   const __amdgpu_buffer_rsrc_t xbuf =
       dma_buffer(X + static_cast<size_t>(j0) * hid, static_cast<uint32_t>(min(kBigRows, T - j0)) * hid * 2u);
-  // copy q of a wave fills rows 8 (8 wave + q) .. + 7 of a slot
-  uint32_t voff[8];
+  // copy q of a wave fills rows 8 (LI wave + q) .. + 7 of a slot
+  uint32_t voff[LI];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const int row = 8 * (8 * wave + q) + (lane >> 3);
+  for (int q = 0; q < LI; ++q) {
+    const int row = 8 * (LI * wave + q) + (lane >> 3);
     voff[q] = static_cast<uint32_t>(row) * hid * 2u + (((lane & 7) ^ big_swz(row)) << 4);
   }
   auto soff = [&](int stage) {
@@ -532,86 +532,89 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_gemm256_kernel(
     ks = ks >= nst ? ks - nst : ks;
     return ks * (kGemmBK * 2);
   };
-  auto copy_w = [&](uint8_t* slot, int q, int so) { buf_dma16_at(wbuf, voff[q], so, slot + (8 * wave + q) * 1024); };
-  auto copy_x = [&](uint8_t* slot, int q, int so) { buf_dma16_at(xbuf, voff[q], so, slot + (8 * wave + q) * 1024); };
+  auto copy_w = [&](uint8_t* slot, int q, int so) { buf_dma16_at(wbuf, voff[q], so, slot + (LI * wave + q) * 1024); };
+  auto copy_x = [&](uint8_t* slot, int q, int so) { buf_dma16_at(xbuf, voff[q], so, slot + (LI * wave + q) * 1024); };
 
-  f32x16 acc[4][4];
+  f32x16 acc[MB][MB];
 #pragma unroll
-  for (int mi = 0; mi < 4; ++mi)
+  for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni)
+    for (int ni = 0; ni < MB; ++ni)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
   auto pin_acc = [&]() {   // (see gemm_tile)
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
+    for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
-      for (int ni = 0; ni < 4; ++ni) asm volatile("" : "+a"(acc[mi][ni]));
+      for (int ni = 0; ni < MB; ++ni) asm volatile("" : "+a"(acc[mi][ni]));
   };
-  // fragment f of k-step j of a stage: W block f (f < 4) or X block f - 4, 32
+  // fragment f of k-step j of a stage: W block f (f < MB) or X block f - MB, 32
   // rows, chunk 2 j + lh
-  bf16x8 frag[2][8];
-  const int arow = (wm * 128 + li) * 128, brow = (wn * 128 + li) * 128;
+  bf16x8 frag[2][2 * MB];
+  const int arow = (wm * 32 * MB + li) * 128, brow = (wn * 32 * MB + li) * 128;
   auto read = [&](bf16x8& out, const uint8_t* ws, const uint8_t* xs, int j, int f) {
     const int pos = ((2 * j + lh) ^ big_swz(li)) << 4;
-    out = as_bf16x8(*reinterpret_cast<const u32x4*>(f < 4 ? ws + arow + f * 4096 + pos
-                                                          : xs + brow + (f - 4) * 4096 + pos));
+    out = as_bf16x8(*reinterpret_cast<const u32x4*>(f < MB ? ws + arow + f * 4096 + pos
+                                                           : xs + brow + (f - MB) * 4096 + pos));
   };
   auto mfma = [&](int set, int i) {
-    const int mi = i >> 2, ni = i & 3;
+    const int mi = i / MB, ni = i % MB;
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0"
                  : "+a"(acc[mi][ni])
-                 : "v"(frag[set][mi]), "v"(frag[set][4 + ni])
+                 : "v"(frag[set][mi]), "v"(frag[set][MB + ni])
                  : "memory");
   };
-  // the products of one k-step, the next one's fragment reads and four of the
+  // the products of one k-step, the next one's fragment reads and MB of the
   // copies issued among them
   auto step = [&](int set, auto reads, auto copies) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < MB * MB; ++i) {
       mfma(set, i);
-      if (i < 8) reads(i);
-      else if (i % 2 == 0) copies((i - 8) / 2);
+      if (i < 2 * MB) reads(i);
+      if (MB == 4 ? i >= 8 && i % 2 == 0 : i >= 2) copies(MB == 4 ? (i - 8) / 2 : i - 2);
     }
   };
   auto none = [](int) {};
 
-  // prologue: stages 0 and 1, and W of stage 2
+  // prologue: the copies of the bodies before stage 0's, in their order
 #pragma unroll
-  for (int q = 0; q < 8; ++q) copy_w(w0, q, soff(0));
+  for (int s = -WR; s < 0; ++s) {
+    if (s + XR >= 0)
 #pragma unroll
-  for (int q = 0; q < 8; ++q) copy_x(x0, q, soff(0));
+      for (int q = 0; q < LI; ++q) copy_x(xring[s + XR], q, soff(s + XR));
 #pragma unroll
-  for (int q = 0; q < 8; ++q) copy_w(w1, q, soff(1));
-#pragma unroll
-  for (int q = 0; q < 8; ++q) copy_x(x1, q, soff(1));
-#pragma unroll
-  for (int q = 0; q < 8; ++q) copy_w(w2, q, soff(2));
+    for (int q = 0; q < LI; ++q) copy_w(wring[s + WR], q, soff(s + WR));
+  }
+  // copies in flight beyond those of stage s + 2 at the end of body s, and
+  // beyond stage 0's before the first products
+  constexpr int kAhead = WR == XR ? (WR - 2) * 2 * LI : LI;
+  constexpr int kAhead0 = WR == XR ? (WR - 1) * 2 * LI : 3 * LI;
   pin_acc();
   mfma_drain();   // the accumulators' zeroing precedes their first product
-  wait_vmcnt<24>();
+  wait_vmcnt<kAhead0>();
   stage_barrier();
 #pragma unroll
-  for (int f = 0; f < 8; ++f) read(frag[0][f], w0, x0, 0, f);
+  for (int f = 0; f < 2 * MB; ++f) read(frag[0][f], w0, x0, 0, f);
 #pragma unroll
   for (int j = 0; j < 3; ++j)
     step(j & 1, [&](int f) { read(frag[(j & 1) ^ 1][f], w0, x0, j + 1, f); }, none);
-  wait_vmcnt<8>();
+  wait_vmcnt<kAhead>();
   stage_barrier();
-  // body s (K = s mod 6): the last k-step of stage s and the first three of
-  // stage s + 1, X of stage s + 2 and W of s + 3 into the slots stage s left
+  // body s (K = s mod U): the last k-step of stage s and the first three of
+  // stage s + 1, X of stage s + XR and W of s + WR into the slots stage s left
+  constexpr int U = WR == XR ? WR : WR * XR;
   auto body = [&](auto kc, int s) {
     constexpr int K = decltype(kc)::value;
-    uint8_t* const wn_ = wring[(K + 1) % 3];
-    uint8_t* const xn_ = xring[(K + 1) % 2];
-    uint8_t* const wf = wring[K % 3];
-    uint8_t* const xf = xring[K % 2];
-    const int sx = soff(s + 2), sw = soff(s + 3);
+    uint8_t* const wn_ = wring[(K + 1) % WR];
+    uint8_t* const xn_ = xring[(K + 1) % XR];
+    uint8_t* const wf = wring[K % WR];
+    uint8_t* const xf = xring[K % XR];
+    const int sx = soff(s + XR), sw = soff(s + WR);
     step(1, [&](int f) { read(frag[0][f], wn_, xn_, 0, f); }, [&](int q) { copy_x(xf, q, sx); });
-    step(0, [&](int f) { read(frag[1][f], wn_, xn_, 1, f); }, [&](int q) { copy_x(xf, 4 + q, sx); });
+    step(0, [&](int f) { read(frag[1][f], wn_, xn_, 1, f); }, [&](int q) { copy_x(xf, MB + q, sx); });
     step(1, [&](int f) { read(frag[0][f], wn_, xn_, 2, f); }, [&](int q) { copy_w(wf, q, sw); });
-    step(0, [&](int f) { read(frag[1][f], wn_, xn_, 3, f); }, [&](int q) { copy_w(wf, 4 + q, sw); });
-    wait_vmcnt<8>();   // all but W of stage s + 3; and this wave's fragments are here
+    step(0, [&](int f) { read(frag[1][f], wn_, xn_, 3, f); }, [&](int q) { copy_w(wf, MB + q, sw); });
+    wait_vmcnt<kAhead>();   // stage s + 2 has landed, and this wave's fragments are here
     stage_barrier();
   };
   using I0 = std::integral_constant<int, 0>;
@@ -620,20 +623,25 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_gemm256_kernel(
   using I3 = std::integral_constant<int, 3>;
   using I4 = std::integral_constant<int, 4>;
   using I5 = std::integral_constant<int, 5>;
+  static_assert(U == 4 || U == 6, "bodies of a round");
   int c = 0;
-  for (; c + 6 < nst; c += 6) {
+  for (; c + U < nst; c += U) {
     body(I0{}, c);
     body(I1{}, c + 1);
     body(I2{}, c + 2);
     body(I3{}, c + 3);
-    body(I4{}, c + 4);
-    body(I5{}, c + 5);
+    if constexpr (U == 6) {
+      body(I4{}, c + 4);
+      body(I5{}, c + 5);
+    }
   }
   if (c + 1 < nst) body(I0{}, c);
   if (c + 2 < nst) body(I1{}, c + 1);
   if (c + 3 < nst) body(I2{}, c + 2);
-  if (c + 4 < nst) body(I3{}, c + 3);
-  if (c + 5 < nst) body(I4{}, c + 4);
+  if constexpr (U == 6) {
+    if (c + 4 < nst) body(I3{}, c + 3);
+    if (c + 5 < nst) body(I4{}, c + 4);
+  }
   step(1, none, none);
   mfma_drain();
   pin_acc();
@@ -641,14 +649,14 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_gemm256_kernel(
 
   // lane (batch row li, half lh) of block (mi, ni) holds vocabulary rows
   // 8 (r / 4) + 4 lh + r % 4
-  const int vbase = r0 + wm * 128 + 4 * lh;
+  const int vbase = r0 + wm * 32 * MB + 4 * lh;
   if (logits) {
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi) {
+    for (int mi = 0; mi < MB; ++mi) {
       __builtin_amdgcn_sched_barrier(0);   // (one block row at a time, as in gemm_tile)
 #pragma unroll
-      for (int ni = 0; ni < 4; ++ni) {
-        const int node = j0 + wn * 128 + 32 * ni + li;
+      for (int ni = 0; ni < MB; ++ni) {
+        const int node = j0 + wn * 32 * MB + 32 * ni + li;
         if (node >= T) continue;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -674,14 +682,14 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_gemm256_kernel(
     __syncthreads();   // every wave is done with the ring
     StatPart* wpart = reinterpret_cast<StatPart*>(x0);   // [2][kBigRows]
 #pragma unroll
-    for (int ni = 0; ni < 4; ++ni) {
+    for (int ni = 0; ni < MB; ++ni) {
       __builtin_amdgcn_sched_barrier(0);   // one column of blocks at a time
       StatPart p = empty;
       auto value = [&](int mi, int r) {
         return vbase + 32 * mi + 8 * (r >> 2) + (r & 3) < r1 ? acc[mi][ni][r] : -INFINITY;
       };
 #pragma unroll
-      for (int mi = 0; mi < 4; ++mi)
+      for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const float x = value(mi, r);
@@ -691,13 +699,12 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_gemm256_kernel(
         }
       take_max(p.zmax, p.idx, __shfl_xor(p.zmax, 32, 64), __shfl_xor(p.idx, 32, 64));
       if (p.zmax != -INFINITY) {
-        const float my2 = p.zmax * it2;
         float Z = 0.f, S2 = 0.f;
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
+        for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const float y2 = fmaxf(fmaf(value(mi, r), it2, -my2), -1000.f);   // (2^-1000 is 0)
+            const float y2 = fmaxf((value(mi, r) - p.zmax) * it2, -1000.f);   // (2^-1000 is 0)
             const float e = __builtin_amdgcn_exp2f(y2);
             Z += e;
             S2 = fmaf(y2, e, S2);
@@ -707,10 +714,10 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_gemm256_kernel(
       }
       p.Z += __shfl_xor(p.Z, 32, 64);
       p.S += __shfl_xor(p.S, 32, 64);
-      if (lh == 0) wpart[wm * kBigRows + wn * 128 + 32 * ni + li] = p;
+      if (lh == 0) wpart[wm * kBigRows + wn * 32 * MB + 32 * ni + li] = p;
     }
     __syncthreads();
-    if (j0 + tid < T) {
+    if (tid < kBigRows && j0 + tid < T) {
       StatPart q = wpart[tid];
       part_merge(q, wpart[kBigRows + tid], inv_temp);
       StatPart* dst = part + static_cast<size_t>(j0 + tid) * G + kSlices * grp;
@@ -722,14 +729,20 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_gemm256_kernel(
   }
 }
 
-template <bool STATS>
-int32_t launch_gemm256(const uint16_t* X, const uint16_t* W, float* logits, int T, int hid, int V,
-                       int G, float inv_temp, StatPart* part, hipStream_t s) {
-  const int groups = (G + kBigRows / 64 - 1) / (kBigRows / 64);
-  const int passes = (T + kBigRows - 1) / kBigRows;
-  hipLaunchKernelGGL(lm_head_gemm256_kernel<STATS>, dim3((groups + 7) / 8 * passes * 8), dim3(kBigThreads),
-                     0, s, X, W, logits, T, hid, V, G, inv_temp, part);
-  return launch_status("verify_logits (256-row tiles) launch");
+template <int MB, int WR, int XR>
+int32_t launch_square(const uint16_t* X, const uint16_t* W, float* logits, int T, int hid, int V,
+                      int G, float inv_temp, StatPart* part, hipStream_t s) {
+  const int groups = (G + MB - 1) / MB;
+  const int passes = (T + 64 * MB - 1) / (64 * MB);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((groups + 7) / 8 * passes * 8), dim3(kBigThreads), 0, s, X, W,
+                       logits, T, hid, V, G, inv_temp, part);
+  };
+  if (part)
+    go(lm_head_square_kernel<MB, WR, XR, true>);
+  else
+    go(lm_head_square_kernel<MB, WR, XR, false>);
+  return launch_status("verify_logits (square tiles) launch");
 }
 
 template <int BM, int NW, int NST, bool STATS>
@@ -744,13 +757,15 @@ int32_t launch_gemm(const uint16_t* X, const uint16_t* W, float* logits, int T, 
   return launch_status("verify_logits (tiled) launch");
 }
 
-// 256-row blocks: eight waves (4 x 2, two per SIMD) measured 2-3 % faster
-// than four (2 x 2) at 90-544 rows.
+// Eight waves (4 x 2, two per SIMD) measured 2-3 % faster than four (2 x 2)
+// at 90-544 rows.
 constexpr int kWideWaves = 8;
 
 }  // namespace
 
 namespace {
+constexpr int kBigRows = 256;
+
 // 256 x 256 tiles: the last pass of 256 rows is more than half full, and the
 // workgroups (one per CU) fill nine tenths of their rounds.
 bool big_tiles(int T, int G, int cus) {
@@ -777,16 +792,13 @@ int32_t launch_lm_gemm(const entmtp_bf16* hidden, const entmtp_bf16* w_lm, float
   const auto* X = reinterpret_cast<const uint16_t*>(hidden);
   const auto* W = reinterpret_cast<const uint16_t*>(w_lm);
   auto* part = static_cast<StatPart*>(partials);
-  if (big_tiles(T, G, cus))
-    return part ? launch_gemm256<true>(X, W, logits, T, hid, V, G, inv_temp, part, s)
-                : launch_gemm256<false>(X, W, logits, T, hid, V, G, inv_temp, nullptr, s);
+  if (big_tiles(T, G, cus)) return launch_square<4, 3, 2>(X, W, logits, T, hid, V, G, inv_temp, part, s);
+  // no 256-row block for every CU
+  if (G / 4 < cus) return launch_square<2, 4, 4>(X, W, logits, T, hid, V, G, inv_temp, part, s);
   auto go = [&](auto nst) {
     constexpr int NST = decltype(nst)::value;
-    if (G / 4 >= cus)   // 256-row blocks still give every CU one
-      return part ? launch_gemm<256, kWideWaves, NST, true>(X, W, logits, T, hid, V, G, inv_temp, part, s)
-                  : launch_gemm<256, kWideWaves, NST, false>(X, W, logits, T, hid, V, G, inv_temp, nullptr, s);
-    return part ? launch_gemm<128, 4, NST, true>(X, W, logits, T, hid, V, G, inv_temp, part, s)
-                : launch_gemm<128, 4, NST, false>(X, W, logits, T, hid, V, G, inv_temp, nullptr, s);
+    return part ? launch_gemm<256, kWideWaves, NST, true>(X, W, logits, T, hid, V, G, inv_temp, part, s)
+                : launch_gemm<256, kWideWaves, NST, false>(X, W, logits, T, hid, V, G, inv_temp, nullptr, s);
   };
   // the 7B hidden size with its stage count known (in a loop of any count the
   // 256-row tile spills: 1024 rows at a 128256-entry vocabulary 1043 us, not 1025)

@@ -31,17 +31,16 @@ __device__ __forceinline__ void part_merge(StatPart& a, const StatPart& b, float
   int zi = a.idx;
   take_max(zm, zi, b.zmax, b.idx);
   if (zm == -INFINITY) return;   // both empty
-  const float my = zm * inv_temp;
   float Z = 0.f, S = 0.f;
-  if (a.zmax != -INFINITY) {
-    const float ma = a.zmax * inv_temp, f = expf(ma - my);
+  if (a.zmax != -INFINITY) {   // (differences of raw logits: exact or nearly, and 0 for the largest)
+    const float d = (a.zmax - zm) * inv_temp, f = expf(d);
     Z += a.Z * f;
-    S += f * (a.S + (ma - my) * a.Z);
+    S += f * (a.S + d * a.Z);
   }
   if (b.zmax != -INFINITY) {
-    const float mb = b.zmax * inv_temp, f = expf(mb - my);
+    const float d = (b.zmax - zm) * inv_temp, f = expf(d);
     Z += b.Z * f;
-    S += f * (b.S + (mb - my) * b.Z);
+    S += f * (b.S + d * b.Z);
   }
   a = StatPart{zm, Z, S, zi};
 }
@@ -99,9 +98,9 @@ __device__ __forceinline__ void merge_rows(const StatPart* __restrict__ part, co
   }
   // d <= 0; the hardware exponential (a few ulp) is far inside the 1e-3 bar
   // of the statistics.  Branch-free: an empty partial adds zeros.
-  auto add = [&](const StatPart& p, float my, float& z, float& sacc) {
+  auto add = [&](const StatPart& p, float mz, float& z, float& sacc) {
     const bool live = p.zmax != -INFINITY;
-    const float d = live ? p.zmax * inv_temp - my : 0.f;
+    const float d = live ? (p.zmax - mz) * inv_temp : 0.f;
     const float f = live ? __expf(d) : 0.f;
     z += p.Z * f;
     sacc += f * (p.S + d * p.Z);
@@ -145,9 +144,8 @@ __device__ __forceinline__ void merge_rows(const StatPart* __restrict__ part, co
 #pragma unroll
     for (int r = 0; r < R; ++r)
       if (m[r] != -INFINITY) {
-        const float my = m[r] * inv_temp;
 #pragma unroll
-        for (int k = 0; k < P; ++k) add(v[r][k], my, Z[r], S[r]);
+        for (int k = 0; k < P; ++k) add(v[r][k], m[r], Z[r], S[r]);
       }
   } else {
 #pragma unroll
@@ -161,8 +159,7 @@ __device__ __forceinline__ void merge_rows(const StatPart* __restrict__ part, co
     for (int r = 0; r < R; ++r)
       if (row[r] >= 0 && m[r] != -INFINITY) {
         const StatPart* src = part + static_cast<size_t>(row[r]) * G;
-        const float my = m[r] * inv_temp;
-        for (int g = lane; g < G; g += 64) add(src[g], my, Z[r], S[r]);
+        for (int g = lane; g < G; g += 64) add(src[g], m[r], Z[r], S[r]);
       }
   }
 #pragma unroll
