@@ -15,8 +15,8 @@
 //  * K advances in stages of 64: each wave loads its share of a stage's W
 //    and X rows into VGPRs (8 rows x 128 bytes per instruction) two stages
 //    ahead of storing them into one of three LDS slots, two stages ahead of
-//    their use (direct global->LDS copies measured at a third of the rate
-//    this tile consumes; 16 rows x 64 bytes per instruction at two thirds);
+//    their use (direct global->LDS copies of 16 rows x 64 bytes measured at a
+//    third of the rate this tile consumes, loads of that shape at two thirds);
 //  * within a 128-byte row the eight 16-byte chunks are stored XOR-swizzled
 //    by the row's place in its 16-row group, so the MFMA fragment reads
 //    (16 rows, one chunk) spread over all LDS banks;

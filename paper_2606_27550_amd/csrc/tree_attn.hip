@@ -51,7 +51,6 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int HD = ENTMTP_HEAD_DIM;  // 128
 constexpr int kAttnThreads = 256;
-constexpr int kAttnWaves = 4;
 constexpr int KB = 32;               // keys per block
 constexpr int kQTile = 32;           // query rows per tile
 constexpr float kLazyLog2 = 8.f;     // the running max is raised only past this many doublings
