@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kSpecThreads) void accept_stochastic_kernel(
   auto load_row = [&](const float* row, float (&x)[kSpecRegs]) {
     const __amdgpu_buffer_rsrc_t buf = dma_buffer(row, static_cast<uint32_t>(V) * 4u);
 #pragma unroll
-    for (int i = 0; i < kSpecRegs; ++i) x[i] = buf_load(buf, tid * 4u, i * kSpecThreads * 4);
+    for (int i = 0; i < kSpecRegs; ++i) x[i] = buf_load(buf, (tid + i * kSpecThreads) * 4u);
   };
   __syncthreads();
   int cur = 0;

@@ -38,8 +38,9 @@ __device__ __forceinline__ void lds_dma16(const void* src, void* lds) {
   __builtin_amdgcn_global_load_lds(src, lds, 16, 0, 0);
 }
 
-// The same copy through a buffer descriptor (lane l from byte voff(l) of the
-// buffer; bytes past its end arrive as zeros).  global_load_lds counts as a flat access, beside which the
+// The same copy through a buffer descriptor (lane l from byte voff(l) + soff of
+// the buffer; lanes whose voff lies past its end receive zeros, and a caller
+// keeps voff + soff below it for the others).  global_load_lds counts as a flat access, beside which the
 // compiler makes every wait for an ordinary load a full drain; beside buffer
 // copies its counted waits stay exact, and the address is one 32-bit offset.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t dma_buffer(const void* base, uint32_t bytes) {
@@ -53,9 +54,11 @@ __device__ __forceinline__ void buf_dma16(__amdgpu_buffer_rsrc_t buf, uint32_t v
   buf_dma16_at(buf, voff, 0, lds);
 }
 
-// Four bytes at byte voff + soff of the buffer (zero past its end).
-__device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t buf, uint32_t voff, int soff) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(buf, static_cast<int>(voff), soff, 0));
+// Four bytes at byte voff of the buffer (zero past its end).  The range check
+// is relied on for the per-lane offset alone: the scalar offset, which it need
+// not cover, stays zero.
+__device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t buf, uint32_t voff) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(buf, static_cast<int>(voff), 0, 0));
 }
 
 // Workgroup barrier without a memory-model fence.  __syncthreads() would add
