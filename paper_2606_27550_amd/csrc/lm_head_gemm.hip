@@ -704,7 +704,8 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_square_kernel(
         for (int mi = 0; mi < MB; ++mi)
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const float y2 = fmaxf((value(mi, r) - p.zmax) * it2, -1000.f);   // (2^-1000 is 0)
+            const float y = (value(mi, r) - p.zmax) * it2;
+            const float y2 = y < -1000.f ? -1000.f : y;   // (2^-1000 is 0; a NaN stays, as fmaxf's would not)
             const float e = __builtin_amdgcn_exp2f(y2);
             Z += e;
             S2 = fmaf(y2, e, S2);
