@@ -364,7 +364,8 @@ __device__ __forceinline__ void gemm_tile(
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             if (full || vbase + 16 * mi + r < r1) {
-              const float y2 = (acc[mi][ni][r] - p.zmax) * it2;
+              const float y = (acc[mi][ni][r] - p.zmax) * it2;
+              const float y2 = y < -1000.f ? -1000.f : y;   // (2^-1000 is 0, and so is a logit of -inf; a NaN stays)
               const float e = __builtin_amdgcn_exp2f(y2);
               Z += e;
               S2 = fmaf(y2, e, S2);

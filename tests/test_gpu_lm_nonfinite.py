@@ -8,12 +8,13 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+from oracle import entmtp_oracle as orc  # noqa: E402
 from paper_2606_27550_amd import synth  # noqa: E402
 from tests import test_gpu_lm_tiled as tiled  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
-BF_ONE, BF_INF, BF_NAN = 0x3F80, 0x7F80, 0x7FC0
+BF_ONE, BF_INF, BF_NEG_INF, BF_NAN = 0x3F80, 0x7F80, 0xFF80, 0x7FC0
 FORMS = [(100, 512, 5000), (140, 512, 5000), (385, 512, 17000), (70, 512, 50000), (300, 1024, 66001)]
 
 
@@ -58,3 +59,18 @@ def test_nan_and_inf_logits_show(api, T, hid, V, bits):
         assert np.isnan(H).all() and np.isnan(p1).all()
         if bits == BF_INF:
             assert (am == row).all()
+
+
+@pytest.mark.parametrize("T,hid,V", FORMS)
+def test_rows_masked_to_minus_inf(api, T, hid, V):
+    X, w = inputs(T, hid, V)
+    masked = [0, 1, V // 2, V - 1]
+    w[masked, 0] = BF_NEG_INF
+    print("[gpu-test] LM head masked rows", T, hid, V, flush=True)
+    for it in (1.0, 1 / 0.7):
+        z, H, p1, am = stats(api, X, w, it)
+        assert (z[:, masked] == -np.inf).all() and np.isfinite(np.delete(z, masked, 1)).all()
+        rH, rp1, ram = orc.logit_stats(z, it)
+        np.testing.assert_array_equal(am, ram)
+        assert np.all(np.abs(H - rH) <= tiled.RTOL_STATS * np.abs(rH) + 1e-6)
+        assert np.all(np.abs(p1 - rp1) <= tiled.RTOL_STATS * np.abs(rp1) + 1e-6)
