@@ -412,12 +412,16 @@ inline void set_rope(BatchArgs& a, float rope_theta) {
   std::copy(freq, freq + kRopePairs, a.freq);
 }
 // sin and cos of x in fp64, 0 <= x < 2^31 (positions times frequencies up to
-// one radian): x less the nearest multiple n of pi/2 (pi/2 as a sum of two
+// one radian, those of a base of one or more): x less the nearest multiple n of pi/2 (pi/2 as a sum of two
 // doubles, each product exact in its fused multiply-add: the remainder is
 // off by a rounding of its own size), then the Taylor series on [-pi/4,
 // pi/4], cut where the next term is below 1e-17 of the value.  About 40 fp64
 // instructions; the library's sincos, made for all arguments, took most of
-// the attention kernels' prologue.
+// the attention kernels' prologue.  It stays for bases below one, whose
+// frequencies grow to 1 / base: the angle of an ordinary position then leaves
+// this range (base 1e-6: from position 4200 on), so those calls have an
+// instance of the kernel of their own (wide_angles) and the others keep theirs
+// as it is.
 __device__ __forceinline__ double2 cos_sin(double x) {
   const double n = rint(x * 0.63661977236758134308);   // 2 / pi
   const double r = fma(-n, 6.123233995736766035869e-17, fma(-n, 1.57079632679489655800, x));
@@ -445,15 +449,25 @@ __device__ __forceinline__ double2 cos_sin(double x) {
   return make_double2(q == 1 || q == 2 ? -a : a, q >= 2 ? -b : b);
 }
 
+inline bool wide_angles(double theta) { return theta > 0.0 && theta < 1.0; }
+
 // Calls put(d, c, (cos, sin)) for the angles of positions L + d, d = 0..D,
 // over the workgroup.  f: this thread's pair frequency, freq[threadIdx.x %
 // 64], loaded by the caller ahead of its bulk loads (a load issued behind
 // them would wait for them).
-template <typename F>
+template <bool WIDE, typename F>
 __device__ __forceinline__ void rope_table(int D, int L, double f, F put) {
   const int c = threadIdx.x % kRopePairs;
-  for (int d = threadIdx.x / kRopePairs; d <= D; d += kAttnThreads / kRopePairs)
-    put(d, c, cos_sin((static_cast<double>(L) + static_cast<double>(d)) * f));
+  for (int d = threadIdx.x / kRopePairs; d <= D; d += kAttnThreads / kRopePairs) {
+    const double x = (static_cast<double>(L) + static_cast<double>(d)) * f;
+    if constexpr (WIDE) {
+      double sn, cs;
+      sincos(x, &sn, &cs);
+      put(d, c, make_double2(cs, sn));
+    } else {
+      put(d, c, cos_sin(x));
+    }
+  }
 }
 
 // Turns the 8 pairs (c0 + e, c0 + e + 64), e < 8, whose halves lo / hi hold
@@ -538,7 +552,8 @@ __device__ __forceinline__ float max_halves(float x) {
 __device__ __forceinline__ int k_swz(int r) { return r & 15; }
 __device__ __forceinline__ int v_swz(int r) { return 4 * (r & 3); }
 
-template <bool DEVB>
+// WIDE: the rotation's angles may pass the short sine's range (wide_angles).
+template <bool DEVB, bool WIDE>
 __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_kernel(BatchArgs p) {
   // blockIdx -> sequence, then (kv head, split) group and query-tile group;
   // the query groups of one (head, split) land on the same XCD (dispatch is
@@ -686,7 +701,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_kernel(BatchArgs p)
   asm volatile("" : "+v"(freq));   // (the compiler would sink its load below the copies)
   float2* const tab32 = reinterpret_cast<float2*>(slot3);
   static_assert((ENTMTP_D_MAX + 1) * kRopePairs * sizeof(float2) <= kRingSlot, "the angles fit in a slot");
-  if (rope) rope_table(sq.D, L, freq, [&](int d, int pr, double2 cs) {
+  if (rope) rope_table<WIDE>(sq.D, L, freq, [&](int d, int pr, double2 cs) {
     tab32[d * kRopePairs + (pr ^ (2 * (d & 31)))] = make_float2(static_cast<float>(cs.x), static_cast<float>(cs.y));
   });
   s_depth[tid] = static_cast<uint8_t>(tdepth);
@@ -848,7 +863,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_kernel(BatchArgs p)
   if (nb > np) {
     __syncthreads();
     if (rope) {
-      rope_table(sq.D, L, freq, [&](int d, int pr, double2 cs) { tab64(d)[pr ^ ((pr >> 3) & 7)] = cs; });
+      rope_table<WIDE>(sq.D, L, freq, [&](int d, int pr, double2 cs) { tab64(d)[pr ^ ((pr >> 3) & 7)] = cs; });
       __syncthreads();
     }
     tree_stage(slot0, tregs, np);
@@ -987,7 +1002,11 @@ size_t al256(size_t x) { return (x + 255) & ~size_t(255); }
 
 template <bool DEVB = false>
 void launch_attend(const BatchArgs& a, int items, hipStream_t s) {
-  hipLaunchKernelGGL(tree_attn_kernel<DEVB>, dim3(items), dim3(kAttnThreads), 0, s, a);
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(items), dim3(kAttnThreads), 0, s, a); };
+  if (wide_angles(a.theta))
+    go(tree_attn_kernel<DEVB, true>);
+  else
+    go(tree_attn_kernel<DEVB, false>);
 }
 
 int device_cus() {
