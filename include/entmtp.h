@@ -229,8 +229,9 @@ int32_t entmtp_tree_attn_batched(const entmtp_bank* bank, int32_t B, const int32
  * arrays of B device pointers, each [Hkv][cap][d] bf16.  Each sequence is
  * computed exactly as entmtp_tree_attn_batched computes it for the same
  * trees and prefix lengths (the kernels derive the same plan).  The grids
- * are sized on the host for the bank's largest plan (trees up to the
- * bank's largest, prefix lengths up to cap - T).  A sequence whose topo[b]
+ * are sized on the host for the longest plan of sequences whose rows do not
+ * overlap (at most rows_cap rows together, prefix lengths up to cap - T);
+ * sequences that share rows are computed too, in more rounds.  A sequence whose topo[b]
  * lies outside the bank, whose prefix_len[b] is negative or leaves fewer
  * than T free cache slots, or whose tree rows do not lie in [row_off[b],
  * row_off[b + 1]) and rows_cap computes nothing (its out rows and cache are

@@ -272,7 +272,8 @@ __device__ __forceinline__ long long uniform(long long x) {
 }
 
 // The sequence that owns index x of a device-planned batch's attend or merge
-// grid (MERGE), its plan included; T = 0 for an index past the last.  Lane i
+// grid (MERGE), its plan included; T = 0 for an index past the last; total:
+// where the indexes end.  Lane i
 // of each wavefront reads sequence i's entries; a sequence whose tree index
 // lies outside the bank, whose prefix length is negative or leaves no room
 // for its tree in the cache, or whose tree rows [row_off[b], row_off[b] + T)
@@ -284,8 +285,8 @@ __device__ __forceinline__ long long uniform(long long x) {
 // workgroups took as long as the attention (185 us a call against 109
 // planned on the host).  Called by whole wavefronts.
 template <bool MERGE>
-__device__ __forceinline__ SeqPlan resolve_batch(const BatchArgs& p, int x) {
-  const int lane = threadIdx.x & 63;
+__device__ __forceinline__ SeqPlan resolve_batch(const BatchArgs& p, int x, int tid, int& total) {
+  const int lane = tid & 63;
   int tr = -1, L = -1, r0 = -1, r1 = -1;
   if (lane < p.B) {
     tr = p.topo_dev[lane];
@@ -362,6 +363,7 @@ __device__ __forceinline__ SeqPlan resolve_batch(const BatchArgs& p, int x) {
   }
   const unsigned long long past = __ballot(lane < p.B && x >= last);
   const int b = __popcll(past);
+  total = __builtin_amdgcn_readlane(last, p.B - 1);
   SeqPlan q = p.s[b < p.B ? b : 0];   // caches and the partial range
   if (b >= p.B) {
     q.T = 0;
@@ -385,13 +387,31 @@ __device__ __forceinline__ SeqPlan resolve_batch(const BatchArgs& p, int x) {
   return q;
 }
 
-// Plan of the sequence that owns index x of the attend or (MERGE) merge grid.
-template <bool DEVB, bool MERGE>
-__device__ __forceinline__ SeqPlan plan_of(const BatchArgs& p, int x) {
-  if constexpr (DEVB)
-    return resolve_batch<MERGE>(p, x);
-  else
-    return resolve(p, seq_of(p, x, [](const SeqPlan& q) { return MERGE ? q.merge0 : q.item0; }));
+// Calls work(plan, x, thread) for the index x this workgroup has in the attend
+// or (MERGE) merge grid.  A device-planned batch's grid is as long as any plan
+// of sequences whose rows are their own; where row ranges overlap (the entries
+// are the device's) the plan can be longer, and a workgroup takes every
+// gridDim.x-th index.
+template <bool DEVB, bool MERGE, typename F>
+__device__ __forceinline__ void for_items(const BatchArgs& p, F work) {
+  int x = static_cast<int>(blockIdx.x);
+  if constexpr (DEVB) {
+    while (true) {
+      // (the thread's number anew each time: what follows from it would
+      // otherwise be kept for the next round, in registers that spilled)
+      int tid = static_cast<int>(threadIdx.x), total;
+      asm volatile("" : "+v"(tid));
+      const SeqPlan sq = resolve_batch<MERGE>(p, x, tid, total);
+      if (sq.T == 0) return;
+      work(sq, x, tid);
+      x += static_cast<int>(gridDim.x);
+      if (x >= total) return;
+      __syncthreads();   // the LDS of one index is read out
+    }
+  } else {
+    work(resolve(p, seq_of(p, x, [](const SeqPlan& q) { return MERGE ? q.merge0 : q.item0; })), x,
+         static_cast<int>(threadIdx.x));
+  }
 }
 
 // ------------------------------------------------------------------ RoPE --
@@ -452,13 +472,12 @@ __device__ __forceinline__ double2 cos_sin(double x) {
 inline bool wide_angles(double theta) { return theta > 0.0 && theta < 1.0; }
 
 // Calls put(d, c, (cos, sin)) for the angles of positions L + d, d = 0..D,
-// over the workgroup.  f: this thread's pair frequency, freq[threadIdx.x %
-// 64], loaded by the caller ahead of its bulk loads (a load issued behind
+// over the workgroup.  f: thread tid's pair frequency, freq[tid % 64], loaded by the caller ahead of its bulk loads (a load issued behind
 // them would wait for them).
 template <bool WIDE, typename F>
-__device__ __forceinline__ void rope_table(int D, int L, double f, F put) {
-  const int c = threadIdx.x % kRopePairs;
-  for (int d = threadIdx.x / kRopePairs; d <= D; d += kAttnThreads / kRopePairs) {
+__device__ __forceinline__ void rope_table(int tid, int D, int L, double f, F put) {
+  const int c = tid % kRopePairs;
+  for (int d = tid / kRopePairs; d <= D; d += kAttnThreads / kRopePairs) {
     const double x = (static_cast<double>(L) + static_cast<double>(d)) * f;
     if constexpr (WIDE) {
       double sn, cs;
@@ -496,7 +515,8 @@ __device__ __forceinline__ void rope_pairs(u32x4& lo, u32x4& hi, const double2* 
 // The same turn of pairs c0 .. c0 + 7 in fp32 with fp32 angles (pair c at
 // t[c ^ swz]: lanes at other depths read other banks), rounded to bf16 by the hardware
 // (for the queries, which only enter bf16 products: the cache keeps the
-// fp64 form's keys).
+// fp64 form's keys).  Which product is fused is spelled out, so that every
+// instance of the kernel rounds alike.
 __device__ __forceinline__ void rope_pairs_f32(u32x4& lo, u32x4& hi, const float2* t, int c0, int swz) {
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
@@ -505,9 +525,9 @@ __device__ __forceinline__ void rope_pairs_f32(u32x4& lo, u32x4& hi, const float
     const float x0 = bf16_lo(lo[w]), x1 = bf16_hi(lo[w]);
     const float y0 = bf16_lo(hi[w]), y1 = bf16_hi(hi[w]);
     lo[w] = __builtin_bit_cast(uint32_t, __builtin_convertvector(
-                                             (f32x2{x0 * a0.x - y0 * a0.y, x1 * a1.x - y1 * a1.y}), bf16x2));
+                                             (f32x2{fmaf(x0, a0.x, -(y0 * a0.y)), fmaf(x1, a1.x, -(y1 * a1.y))}), bf16x2));
     hi[w] = __builtin_bit_cast(uint32_t, __builtin_convertvector(
-                                             (f32x2{y0 * a0.x + x0 * a0.y, y1 * a1.x + x1 * a1.y}), bf16x2));
+                                             (f32x2{fmaf(x0, a0.y, y0 * a0.x), fmaf(x1, a1.y, y1 * a1.x)}), bf16x2));
   }
 }
 
@@ -553,22 +573,21 @@ __device__ __forceinline__ int k_swz(int r) { return r & 15; }
 __device__ __forceinline__ int v_swz(int r) { return 4 * (r & 3); }
 
 // WIDE: the rotation's angles may pass the short sine's range (wide_angles).
-template <bool DEVB, bool WIDE>
-__global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_kernel(BatchArgs p) {
+template <bool WIDE>
+__device__ __forceinline__ void attend_item(const BatchArgs& p, const SeqPlan& sq, int x, int tid) {
   // blockIdx -> sequence, then (kv head, split) group and query-tile group;
   // the query groups of one (head, split) land on the same XCD (dispatch is
   // round-robin over 8 XCDs and every sequence's range starts at a multiple
   // of 8), so their K/V reads share that XCD's L2.
-  const SeqPlan sq = plan_of<DEVB, false>(p, static_cast<int>(blockIdx.x));
   if (sq.T == 0) return;
-  const int bid = blockIdx.x - sq.item0;
+  const int bid = x - sq.item0;
   const int qg = (bid >> 3) % sq.nqg;
   const int gc = ((bid >> 3) / sq.nqg) * 8 + (bid & 7);
   if (gc >= p.Hkv * sq.nsplit) return;
   const int g = gc / sq.nsplit, split = gc % sq.nsplit;
   const int T = sq.T, L = sq.L, nkeys = sq.L + sq.T, rows_pad = sq.rows_pad;
   const int nsplit = sq.nsplit;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = tid >> 6;
   const int li = lane & 31, lh = lane >> 5;
   const int GT = p.G * T;
   const int qt = qg * 4 + wave;           // this wave's query tile
@@ -701,7 +720,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_kernel(BatchArgs p)
   asm volatile("" : "+v"(freq));   // (the compiler would sink its load below the copies)
   float2* const tab32 = reinterpret_cast<float2*>(slot3);
   static_assert((ENTMTP_D_MAX + 1) * kRopePairs * sizeof(float2) <= kRingSlot, "the angles fit in a slot");
-  if (rope) rope_table<WIDE>(sq.D, L, freq, [&](int d, int pr, double2 cs) {
+  if (rope) rope_table<WIDE>(tid, sq.D, L, freq, [&](int d, int pr, double2 cs) {
     tab32[d * kRopePairs + (pr ^ (2 * (d & 31)))] = make_float2(static_cast<float>(cs.x), static_cast<float>(cs.y));
   });
   s_depth[tid] = static_cast<uint8_t>(tdepth);
@@ -863,7 +882,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_kernel(BatchArgs p)
   if (nb > np) {
     __syncthreads();
     if (rope) {
-      rope_table<WIDE>(sq.D, L, freq, [&](int d, int pr, double2 cs) { tab64(d)[pr ^ ((pr >> 3) & 7)] = cs; });
+      rope_table<WIDE>(tid, sq.D, L, freq, [&](int d, int pr, double2 cs) { tab64(d)[pr ^ ((pr >> 3) & 7)] = cs; });
       __syncthreads();
     }
     tree_stage(slot0, tregs, np);
@@ -923,6 +942,11 @@ __global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_kernel(BatchArgs p)
     }
 }
 
+template <bool DEVB, bool WIDE>
+__global__ __launch_bounds__(kAttnThreads, 2) void tree_attn_kernel(BatchArgs p) {
+  for_items<DEVB, false>(p, [&](const SeqPlan& sq, int x, int tid) { attend_item<WIDE>(p, sq, x, tid); });
+}
+
 // ----------------------------------------------------------------- merge --
 
 // One half-wavefront per output row (kMergeRows rows per block): lane c <
@@ -936,15 +960,13 @@ constexpr int kMergeBatch = 16;   // splits whose partials are requested togethe
 constexpr int kMergeThreads = 32 * kMergeRows;
 static_assert(kMaxSplits <= 32, "a half-wavefront holds one lane per split");
 
-template <bool DEVB>
-__global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(BatchArgs p) {
-  const SeqPlan sq = plan_of<DEVB, true>(p, static_cast<int>(blockIdx.x));
+__device__ __forceinline__ void merge_item(const BatchArgs& p, const SeqPlan& sq, int x, int tid) {
   if (sq.nsplit == 1 || sq.T == 0) return;   // written by the attend kernel, or nothing to do
   const int GT = p.G * sq.T;
-  const int local = (blockIdx.x - sq.merge0) * kMergeRows + (threadIdx.x >> 5);
+  const int local = (x - sq.merge0) * kMergeRows + (tid >> 5);
   if (local >= p.Hkv * GT) return;   // past the last row (device-planned grids cover the largest tree)
   const int g = local / GT, row = local % GT;
-  const int lane = threadIdx.x & 31;
+  const int lane = tid & 31;
   const int nsplit = sq.nsplit;
   auto prow_of = [&](int c) {
     return sq.part_off + (static_cast<size_t>(c) * p.Hkv + g) * sq.rows_pad + row;
@@ -994,6 +1016,11 @@ __global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(BatchArgs p) 
   pk.x = f32_to_bf16_rne(acc.x) | (f32_to_bf16_rne(acc.y) << 16);
   pk.y = f32_to_bf16_rne(acc.z) | (f32_to_bf16_rne(acc.w) << 16);
   *reinterpret_cast<uint2*>(p.out + (static_cast<size_t>(sq.row0 + node) * p.Hq + g * p.G + gh) * HD + d4) = pk;
+}
+
+template <bool DEVB>
+__global__ __launch_bounds__(kMergeThreads) void attn_merge_kernel(BatchArgs p) {
+  for_items<DEVB, true>(p, [&](const SeqPlan& sq, int x, int tid) { merge_item(p, sq, x, tid); });
 }
 
 // ------------------------------------------------------------------ host --
@@ -1260,8 +1287,9 @@ int32_t launch_attn_device(const entmtp_bank* bank, const DevStep* dev, const De
 }
 
 // What the host fixes of a device-planned batch: grids that cover every plan
-// the device can make, and per-sequence partial ranges sized for the largest
-// plan any bank tree can need at prefix lengths up to cap - T.
+// the device can make (of sequences with rows of their own: for_items), and
+// per-sequence partial ranges sized for the largest plan any bank tree can need
+// at prefix lengths up to cap - T.
 struct BatchDevShape {
   int items = 0;             // attend workgroups
   int merge_blocks = 0;
@@ -1277,7 +1305,7 @@ BatchDevShape batch_dev_shape(const entmtp_bank* bank, int B, int Hq, int Hkv, i
   const int bound = split_bound((cap + KB - 1) / KB);
   const int T_max = bank_rows(bank);
   sh.two = two_rounds(streams_bound(B, Hkv, G, static_cast<long long>(B) * T_max), slots);
-  // tree rows of the batch (the sequences' rows are disjoint and within rows_cap)
+  // tree rows of the batch, where no two sequences share one
   const long long rows = std::min<long long>(rows_cap, static_cast<long long>(B) * T_max);
   const long long streams = streams_bound(B, Hkv, G, rows);
   // items of a batch: at most work / t + streams (t at least half the even

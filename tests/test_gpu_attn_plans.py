@@ -136,3 +136,41 @@ def test_batch_host_and_device_plans(api, B, Hq, Hkv, lo, hi):
         assert torch.equal(res[0][1][b], res[1][1][b]) and torch.equal(res[0][2][b], res[1][2][b])
         assert torch.equal(res[0][2][b], vcs[b])
         assert float((res[0][1][b].double() - kcs[b].double()).abs().max()) <= 2.0 ** -6
+
+
+@pytest.mark.parametrize("T,G,Hkv,L,step", [
+    (128, 32, 8, 40, 0),      # unsplit: more attend workgroups than disjoint rows could take
+    (128, 1, 8, 3000, 64),    # split: more merge blocks
+])
+def test_device_batch_sequences_that_share_rows(api, T, G, Hkv, L, step):
+    """Device-planned sequences whose row ranges overlap (a sequence without
+    work between two of them has a range that ends below its start): every
+    sequence is computed, whatever the grids were sized for.  All have the same
+    queries, keys and caches; where rows of different nodes coincide, only those
+    that one sequence alone writes are compared."""
+    print("[gpu-test] device batch of sequences that share rows", T, G, Hkv, flush=True)
+    n = 8
+    parent = [-1] + [0] * (T - 1)
+    bank = api.Bank([parent])
+    rows = T + step * (n - 1)
+    q, k, v = normal(1, T, G * Hkv, D), normal(2, T, Hkv, D), normal(3, T, Hkv, D)
+    if step:   # equal rows, so that every sequence's tree has the same
+        q, k, v = (x[:1].repeat(rows, 1, 1) for x in (q, k, v))
+    kc0, vc0 = normal(4, Hkv, L + T, D), normal(5, Hkv, L + T, D)
+    kc, vc = [kc0.clone() for _ in range(2 * n)], [vc0.clone() for _ in range(2 * n)]
+    out = torch.full_like(q, float("nan"))
+    off = [x for b in range(n) for x in (step * b, step * b + T)] + [0]
+    dev = [torch.tensor(x, dtype=torch.int32, device="cuda") for x in ([0, -1] * n, [L] * 2 * n, off)]
+    ws = torch.empty(api.tree_attn_batched_device_workspace(bank, 2 * n, G * Hkv, Hkv, D, L + T),
+                     dtype=torch.uint8, device="cuda")
+    api.tree_attn_batched_device(bank, *dev, q, k, v, kc, vc, SCALE, THETA, out, ws)
+    rk, rv = kc0.clone(), vc0.clone()
+    ref = reference(parent, q[:T], k[:T], v[:T], rk, rv, L)
+    for b in range(2 * n):
+        assert torch.equal(vc[b], vc0 if b % 2 else rv), b
+        assert torch.equal(kc[b], kc0 if b % 2 else kc[0]), b
+    if step == 0:
+        assert float((out.double() - ref).abs().max()) <= TOL
+    else:   # the rows that one sequence alone writes
+        assert float((out[:step].double() - ref[:step]).abs().max()) <= TOL
+        assert float((out[-step:].double() - ref[-step:]).abs().max()) <= TOL
