@@ -97,12 +97,12 @@ __global__ __launch_bounds__(kStatsThreads) void logit_stats_kernel(
   for (int w = 1; w < kStatsWaves; ++w) take_best(best, bidx, s_v[w], s_i[w]);
 
   // ---- Z = sum e^(y-m), S = sum (y-m) e^(y-m)
-  const float m = best * inv_temp;
+  // (the difference of the raw logits first: exact or nearly, 0 for the largest)
   float Z = 0.f, S = 0.f;
   for (int u0 = 0; u0 < n; u0 += R * kStatsThreads) {
     if (!one) load(u0);
     each(u0, [&](float v, int) {
-      const float t = v * inv_temp - m;
+      const float t = (v - best) * inv_temp;
       const float e = expf(t);
       Z += e;
       if (e > 0.f) S += t * e;  // keeps (-inf) * 0 out of the sum

@@ -90,3 +90,19 @@ def test_stochastic_rows_end_at_the_vocabulary(api, V):
         assert (int(a), int(bonus)) == (ref[0], ref[2])
         assert path.tolist()[: ref[0] + 1] == list(ref[1])
     assert checked >= 3
+
+
+@pytest.mark.parametrize("V", [32000, 50001])
+def test_logit_stats_of_large_logits(api, V):
+    """A lone large logit has probability one at any temperature: its own term
+    is exactly one (temperature times the logit alone would bring a rounding of
+    its own size, 1.5e-5 at 200), the others sum to less than 1e-8."""
+    print("[gpu-test] logit_stats of large logits V", V, flush=True)
+    g = np.random.default_rng(V)
+    z = g.normal(0, 2.5, (40, V)).astype(np.float32)
+    top = g.integers(0, V, 40)
+    z[np.arange(40), top] = g.uniform(100, 300, 40).astype(np.float32)
+    for it in (1 / 0.7, 0.9):
+        H, p1, am = kern.run_stats(api, z, it)
+        np.testing.assert_array_equal(am, top)
+        assert (np.abs(p1 - 1) <= 1e-7).all() and (np.abs(H) <= 1e-6).all()
