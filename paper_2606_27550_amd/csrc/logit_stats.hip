@@ -6,12 +6,13 @@
 // produces the lowest-index argmax, p1 = 1/Z and the entropy
 // H = ln Z - sum (y - m) e^(y - m) / Z with y = inv_temp * z, m = max y.
 //
-// One workgroup per row.  A slab of the row (up to 32768 entries: 64 registers
-// a thread) has all its loads in flight at once, and a row of one slab stays
-// in registers for both steps (max / argmax, then the two sums); longer rows
-// are read twice, the second time from L2.  With a load a loop trip the
-// kernel waited out a memory latency per 2048 entries: 12.9 ->
-// 11.3 us for 26 rows of 32000; the exponentials of one CU are what
+// One workgroup per row.  A slab of the row (up to 32768 entries, 16384 where V
+// is no multiple of four: up to 64 registers a thread) has all its loads in
+// flight at once, and a row of one slab stays in registers for both steps
+// (max / argmax, then the two sums); longer rows are read twice, the second
+// time from L2.  With a load a loop trip the kernel waited out a memory latency
+// per 2048 entries (per 512 where V is no multiple of four): 26 rows of 32000
+// 12.7 -> 11.9 us, of 24001 19.2 -> 13.6; the exponentials of one CU are what
 // is left.  Reductions use wave shuffles and a fixed-order combine of the
 // per-wave results, so the result does not depend on scheduling.
 #include <cfloat>
@@ -35,7 +36,8 @@ __device__ __forceinline__ void take_best(float& v, int& i, float v2, int i2) {
 }
 
 // VEC: V is a multiple of four (rows of 16-byte units), else units of one entry.
-template <bool VEC>
+// R: units per thread and slab.
+template <bool VEC, int R>
 __global__ __launch_bounds__(kStatsThreads) void logit_stats_kernel(
     const float* __restrict__ logits, int V, float inv_temp, float* __restrict__ entropy,
     float* __restrict__ top1p, int* __restrict__ argmax) {
@@ -44,7 +46,6 @@ __global__ __launch_bounds__(kStatsThreads) void logit_stats_kernel(
   __shared__ float s_z[kStatsWaves], s_s[kStatsWaves];
 
   constexpr int E = VEC ? 4 : 1;             // entries per unit
-  constexpr int R = VEC ? 16 : 32;           // units per thread and slab
   const float* z = logits + static_cast<size_t>(blockIdx.x) * V;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -54,6 +55,7 @@ __global__ __launch_bounds__(kStatsThreads) void logit_stats_kernel(
   auto load = [&](int u0) {   // (past the row: its last unit, not used)
 #pragma unroll
     for (int i = 0; i < R; ++i) {
+      if (u0 + kStatsThreads * i >= n) break;   // (uniform)
       const int u = min(u0 + tid + kStatsThreads * i, n - 1);
       if constexpr (VEC) {
         const float4 v = reinterpret_cast<const float4*>(z)[u];
@@ -69,6 +71,7 @@ __global__ __launch_bounds__(kStatsThreads) void logit_stats_kernel(
   auto each = [&](int u0, auto f) {   // f(entry, index) in index order
 #pragma unroll
     for (int i = 0; i < R; ++i) {
+      if (u0 + kStatsThreads * i >= n) break;
       const int u = u0 + tid + kStatsThreads * i;
       if (u < n) {
 #pragma unroll
@@ -149,9 +152,13 @@ extern "C" int32_t entmtp_logit_stats(const float* logits, int32_t T, int32_t V,
     hipLaunchKernelGGL(kernel, dim3(T), dim3(kStatsThreads), 0, static_cast<hipStream_t>(stream), logits,
                        V, inv_temp, entropy, top1p, argmax);
   };
+  // Short rows take a slab of a quarter: at 40 registers a thread instead of 88
+  // four workgroups share a CU, which more rows than CUs need (300 rows of 1000
+  // to 4000 entries 6.3 - 7.1 us in the long form, loads past the row included,
+  // 4.4 - 5.4 in this one); longer rows want every load of theirs in flight.
   if ((V & 3) == 0)
-    go(logit_stats_kernel<true>);
+    V <= 16 * kStatsThreads ? go(logit_stats_kernel<true, 4>) : go(logit_stats_kernel<true, 16>);
   else
-    go(logit_stats_kernel<false>);
+    V <= 8 * kStatsThreads ? go(logit_stats_kernel<false, 8>) : go(logit_stats_kernel<false, 32>);
   return launch_status("logit_stats launch");
 }

@@ -1,7 +1,7 @@
 """GPU tests of the sampling path's kernels at the vocabulary sizes where their
 forms change: a thread's share of one entry, chunk lengths odd and even, the
 largest row kept in LDS and the first beyond it, one and two slabs of a row in
-either width of load.  Decisions against the oracle (inputs redrawn until they
+either width of load and both lengths of slab.  Decisions against the oracle (inputs redrawn until they
 are clear), statistics at the bounds of tests/test_gpu_kernels.py."""
 import numpy as np
 import pytest
@@ -36,7 +36,8 @@ def test_stochastic_vocabulary_sizes(api, V):
         assert path[: a + 1] == list(ref[1])
 
 
-@pytest.mark.parametrize("V", [1, 3, 4, 2047, 2048, 16384, 16385, 32768, 32772, 65537])
+@pytest.mark.parametrize("V", [1, 3, 4, 2047, 2048, 2052, 4095, 4097, 8192, 8196, 16384, 16385, 32768, 32772,
+                               65537])
 def test_logit_stats_slabs(api, V):
     print("[gpu-test] logit_stats V", V, flush=True)
     g = np.random.default_rng(V)
