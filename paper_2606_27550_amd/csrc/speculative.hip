@@ -54,16 +54,24 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return s;
 }
 
-constexpr int kSpecRegs = 32;
-constexpr int kSpecResident = kSpecRegs * kSpecThreads;   // largest vocabulary whose row fits in LDS
+constexpr int kSpecRegs = 32;        // entries a thread of the longest row kept in LDS
+constexpr int kSpecShortRegs = 8;    // and of the short ones
+constexpr int kSpecTinyRegs = 2;
 constexpr int kSpecBatch = 16;                           // else: loads of each row in flight per thread
 constexpr int kSpecSeg = 16;                             // entries of each chunk staged at a time (draw)
 constexpr int kSpecSegLd = kSpecSeg + 1;
 
-// RES: the vocabulary has at most kSpecResident entries.  Dynamic LDS: the
-// resident row (kSpecResident entries and padding), or a segment of every
-// thread's chunk.
-template <bool RES>
+// Dynamic LDS of the form that keeps a row of R entries a thread (and its
+// padding), or with R = 0 a segment of every thread's chunk.
+constexpr size_t spec_lds(int R) {
+  return (R > 0 ? R * kSpecThreads + 3 * (R * kSpecThreads / 32) : kSpecThreads * kSpecSegLd) * sizeof(float);
+}
+
+constexpr size_t kSpecStaticLds = 11 * 1024;   // (the per-node arrays, rounded up)
+static_assert(spec_lds(kSpecRegs) + kSpecStaticLds <= 160 * 1024, "the resident row fits in the LDS of a CU");
+
+// R > 0: the vocabulary has at most R entries a thread, and its row is kept.
+template <int R>
 __global__ __launch_bounds__(kSpecThreads) void accept_stochastic_kernel(
     const int* __restrict__ parent, const int* __restrict__ depth,
     const int* __restrict__ path_tab, int T, int D, const int* __restrict__ tok,
@@ -72,6 +80,8 @@ __global__ __launch_bounds__(kSpecThreads) void accept_stochastic_kernel(
     const float* __restrict__ u_accept, const float* __restrict__ u_sample, float* __restrict__ w,
     int* __restrict__ accept_len, int* __restrict__ path_out, int path_cap,
     int* __restrict__ bonus) {
+  constexpr bool RES = R > 0;
+  constexpr int NR = RES ? R : 1;   // entries a thread
   extern __shared__ float s_row[];
   __shared__ float red[kSpecWaves];
   __shared__ float s_scan[kSpecWaves];
@@ -103,11 +113,11 @@ __global__ __launch_bounds__(kSpecThreads) void accept_stochastic_kernel(
   auto at = [](int v) { return v + 3 * (v >> 5); };
   constexpr int kStride = kSpecThreads + 3 * (kSpecThreads / 32);
   float* const mine_row = s_row + at(tid);
-  // entries tid + 1024 i, i < kSpecRegs, of a row (zeros past its end)
-  auto load_row = [&](const float* row, float (&x)[kSpecRegs]) {
+  // entries tid + 1024 i, i < R, of a row (zeros past its end)
+  auto load_row = [&](const float* row, float (&x)[NR]) {
     const __amdgpu_buffer_rsrc_t buf = dma_buffer(row, static_cast<uint32_t>(V) * 4u);
 #pragma unroll
-    for (int i = 0; i < kSpecRegs; ++i) x[i] = buf_load(buf, (tid + i * kSpecThreads) * 4u);
+    for (int i = 0; i < NR; ++i) x[i] = buf_load(buf, (tid + i * kSpecThreads) * 4u);
   };
   __syncthreads();
   int cur = 0;
@@ -154,10 +164,10 @@ __global__ __launch_bounds__(kSpecThreads) void accept_stochastic_kernel(
     bool loaded = false;   // (RES) s_row holds r
     auto fill = [&]() {
       loaded = true;
-      float a[kSpecRegs];
+      float a[NR];
       load_row(zr, a);
 #pragma unroll
-      for (int i = 0; i < kSpecRegs; ++i) {   // (zeros past the row: they stay so in every residual)
+      for (int i = 0; i < NR; ++i) {   // (zeros past the row: they stay so in every residual)
         mine_row[i * kStride] = tid < V - kSpecThreads * i ? p_of(a[i]) : 0.f;
         if (i % 8 == 7) __builtin_amdgcn_sched_barrier(0);   // (all at once would spill)
       }
@@ -194,10 +204,10 @@ __global__ __launch_bounds__(kSpecThreads) void accept_stochastic_kernel(
       float part = 0.f;
       if constexpr (RES) {
         if (!loaded) fill();
-        float x[kSpecRegs];
+        float x[NR];
         load_row(qr, x);
 #pragma unroll
-        for (int i = 0; i < kSpecRegs; ++i) {
+        for (int i = 0; i < NR; ++i) {
           x[i] = fmaxf(mine_row[i * kStride] - x[i], 0.f);
           part += x[i];
         }
@@ -205,7 +215,7 @@ __global__ __launch_bounds__(kSpecThreads) void accept_stochastic_kernel(
         if (mass > 0.f) {
           resid = true;
 #pragma unroll
-          for (int i = 0; i < kSpecRegs; ++i) {
+          for (int i = 0; i < NR; ++i) {
             mine_row[i * kStride] = x[i] / mass;
             if (i % 8 == 7) __builtin_amdgcn_sched_barrier(0);
           }
@@ -369,11 +379,18 @@ extern "C" int32_t entmtp_accept_stochastic(const entmtp_bank* bank, int32_t top
                        bank_ptr<int>(bank, d.off_path), d.T, d.D, draft_tokens, logits, q, V, inv_temp,
                        argmax, top1p, u_accept, u_sample, workspace, accept_len, path, d.D + 1, bonus);
   };
-  // a row in the LDS of one CU up to kSpecResident entries
-  // (147 KB of it), else a segment at a time
-  if (V <= kSpecResident)
-    go(accept_stochastic_kernel<true>, (kSpecResident + 3 * (kSpecResident / 32)) * sizeof(float));
+  // a row in the LDS of one CU up to 32 entries a thread (140 KB of it), else a
+  // segment at a time.  Short rows have instances of their own: with the long
+  // row's 32 exponentials and divisions a thread a pass over 1000 entries took
+  // 20.5 us a walk of 8 nodes, 9.0 with two (12.0 in a loop of loads), and one
+  // over 4000 11.9, 8.1 with eight (10.5)
+  if (V <= kSpecTinyRegs * kSpecThreads)
+    go(accept_stochastic_kernel<kSpecTinyRegs>, spec_lds(kSpecTinyRegs));
+  else if (V <= kSpecShortRegs * kSpecThreads)
+    go(accept_stochastic_kernel<kSpecShortRegs>, spec_lds(kSpecShortRegs));
+  else if (V <= kSpecRegs * kSpecThreads)
+    go(accept_stochastic_kernel<kSpecRegs>, spec_lds(kSpecRegs));
   else
-    go(accept_stochastic_kernel<false>, static_cast<size_t>(kSpecThreads) * kSpecSegLd * sizeof(float));
+    go(accept_stochastic_kernel<0>, spec_lds(0));
   return launch_status("accept_stochastic launch");
 }

@@ -1,8 +1,9 @@
 """GPU tests of the sampling path's kernels at the vocabulary sizes where their
 forms change: a thread's share of one entry, chunk lengths odd and even, the
-largest row kept in LDS and the first beyond it, one and two slabs of a row in
-either width of load and both lengths of slab.  Decisions against the oracle (inputs redrawn until they
-are clear), statistics at the bounds of tests/test_gpu_kernels.py."""
+largest row kept in LDS at each number of entries a thread and the first beyond
+it, one and two slabs of a row in either width of load and both lengths of slab.
+Decisions against the oracle (inputs redrawn until they are clear), statistics
+at the bounds of tests/test_gpu_kernels.py."""
 import numpy as np
 import pytest
 
@@ -24,7 +25,7 @@ def api():
     return _api
 
 
-@pytest.mark.parametrize("V", [2, 1023, 1025, 30723, 32768, 32769, 50001])
+@pytest.mark.parametrize("V", [2, 1023, 1025, 2048, 2049, 8192, 8193, 30723, 32768, 32769, 50001])
 def test_stochastic_vocabulary_sizes(api, V):
     g = np.random.default_rng(V)
     parent = synth.uniform_attach_tree(17, 24, 3)
