@@ -56,11 +56,13 @@ constexpr int kQTile = 32;           // query rows per tile
 constexpr float kLazyLog2 = 8.f;     // the running max is raised only past this many doublings
 constexpr int kMaxSplits = 32;
 constexpr int kMinBlocksPerSplit = 4;
-// Sequences of up to this many key blocks are not split: a merge costs about
-// as much as ten blocks of one wave's products (launch, partials, its gap).
-// 27 nodes at prefixes 512 and 600: 24.0 us split, 19.2 and 19.8 unsplit; at
-// 700 (split either way) 24.
-constexpr int kLoneBlocks = 20;
+// Sequences of up to this many key blocks are not split: a merge (launch,
+// partials, its gap) costs as much as the blocks it saves.  Captured calls back
+// to back, split / unsplit, 32 KV heads: 9 blocks 12.5 / 12.2 us (27 nodes), 10
+// 14.1 / 14.4 (64), 11 12.3 / 12.9 (7) and 12.5 / 13.0 (27), where calls from
+// Python still gain unsplit (13.9 / 13.1); 12 13.6 / 15.3 (64), 13 12.3 / 14.3,
+// 20 13.7 / 18.9 (27).  4 and 8 KV heads alike.
+constexpr int kLoneBlocks = 11;
 constexpr int kTilesPerWg = 4;       // query tiles per workgroup, one per wave
 constexpr int kWgPerCu = 2;          // attend workgroups resident per CU (registers, LDS)
 constexpr int kMaxSeqs = ENTMTP_B_MAX;

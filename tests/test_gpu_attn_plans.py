@@ -73,7 +73,8 @@ def reference(parent, q, k, v, kc, vc, L):
 @pytest.mark.parametrize("T,L,Hq,Hkv", [
     (1, 0, 2, 2), (1, 31, 2, 2), (7, 32, 4, 2), (32, 96, 2, 2), (33, 127, 2, 2),
     (27, 128, 2, 2), (27, 160, 2, 2),      # ring rounds: 4 and 5 prefix blocks
-    (31, 609, 2, 2), (32, 609, 2, 2),      # 20 and 21 blocks: the unsplit limit
+    (31, 321, 2, 2), (32, 321, 2, 2),      # 11 and 12 blocks: the unsplit limit
+    (31, 609, 2, 2), (32, 609, 2, 2),      # 20 and 21 blocks
     (1, 1023, 3, 3), (1, 1024, 3, 1), (128, 1500, 2, 1), (129, 900, 1, 1), (256, 700, 2, 1),
     (64, 5000, 5, 5), (5, 8191, 28, 4),
 ])
