@@ -802,9 +802,11 @@ int32_t launch_lm_gemm(const entmtp_bf16* hidden, const entmtp_bf16* w_lm, float
     return part ? launch_gemm<256, kWideWaves, NST, true>(X, W, logits, T, hid, V, G, inv_temp, part, s)
                 : launch_gemm<256, kWideWaves, NST, false>(X, W, logits, T, hid, V, G, inv_temp, nullptr, s);
   };
-  // the 7B hidden size with its stage count known (in a loop of any count the
-  // 256-row tile spills: 1024 rows at a 128256-entry vocabulary 1043 us, not 1025)
+  // the 7B and 13B hidden sizes with their stage counts known (in a loop of any
+  // count the 256-row tile spills: 1024 rows at a 128256-entry vocabulary 1043
+  // us, not 1025)
   if (hid == 64 * kGemmBK) return go(std::integral_constant<int, 64>{});
+  if (hid == 80 * kGemmBK) return go(std::integral_constant<int, 80>{});
   return go(std::integral_constant<int, 0>{});
 }
 
