@@ -1,8 +1,10 @@
-"""GPU parity of the tiled LM head at hidden sizes whose stage counts leave
-each remainder of its six-stage round (multiples of 512: two, four or none),
-with ragged batches and vocabularies of odd size (rows of logits at any
-multiple of four bytes), against the oracle at the bounds of
-tests/test_gpu_lm_tiled.py."""
+"""GPU parity of the tiled LM head at hidden sizes of every stage count's
+remainder, with ragged batches and vocabularies of odd size (rows of logits at
+any multiple of four bytes), against the oracle at the bounds of
+tests/test_gpu_lm_tiled.py.  The forms as 256 CUs dispatch them: 128 x 128
+tiles (rounds of four stages, of which a multiple of 512 leaves none), 256 x 256
+and 256 x 128 tiles (rounds of six: none, two or four left; the last with three
+live 16-row blocks of X too)."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -24,6 +26,8 @@ def api():
 @pytest.mark.parametrize("T,hid,V", [
     (129, 512, 16385), (140, 1024, 1027), (65, 1536, 33001), (257, 2048, 16386), (200, 512, 66001),
     (256, 3584, 4099), (385, 1024, 17000),
+    (385, 512, 17000), (400, 1536, 17001),                                          # 256 x 256
+    (70, 512, 50001), (110, 1024, 50001), (130, 1536, 50001), (300, 1024, 66001),   # 256 x 128
 ])
 def test_tiled_hidden_sizes(api, T, hid, V):
     print("[gpu-test] tiled LM head", T, hid, V, flush=True)

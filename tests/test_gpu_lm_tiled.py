@@ -1,4 +1,4 @@
-"""GPU parity of the tiled LM head (the kernel that takes batches of many
+"""GPU parity of the tiled LM head (the kernels that take batches of many
 rows: more than 128, or more than 64 at a 128256-entry vocabulary) against
 the oracle: logits within 1e-4 of the largest |logit|, argmax bit-exact where
 the top-2 gap exceeds fp32 accumulation error, entropy and top-1 probability
@@ -75,9 +75,9 @@ def check_rows(api, X, w, wd, with_logits=True):
 
 def test_tiled_lm_head_logits_only_sampled(api):
     """entmtp_verify_logits (no statistics) at the batched workload's row
-    counts and past 256 rows (300 and 340 leave the waves 3 and 2 live
-    16-row blocks in the last pass): sampled columns, the vocabulary's ends
-    included."""
+    counts and past 256 rows (300 and 340 leave the waves of the first half 3
+    and 4 live 16-row blocks in the last pass, the second half 0 and 2):
+    sampled columns, the vocabulary's ends included."""
     V, hid = 128256, 4096
     w, wd = weight(V, hid)
     cols = np.unique(np.concatenate([np.random.default_rng(3).integers(0, V, 300),
@@ -94,13 +94,16 @@ def test_tiled_lm_head_logits_only_sampled(api):
         assert err <= 1e-4 * max(1.0, np.abs(ref).max()), err
 
 
-@pytest.mark.parametrize("T,hid,V", [(65, 4096, 128256), (90, 4096, 128256), (129, 4096, 128256),
+@pytest.mark.parametrize("T,hid,V", [(65, 4096, 128256), (90, 4096, 128256), (110, 4096, 128256), (129, 4096, 128256),
                                      (400, 4096, 128256), (148, 4096, 32000), (200, 4096, 32000),
                                      (257, 4096, 32000),
                                      (129, 5120, 32000), (300, 5120, 32000)])
 def test_tiled_lm_head_statistics(api, T, hid, V):
-    """Row counts chosen so that the last pass of 128 rows leaves each wave
-    every number (0-4) of live 16-row blocks at both tile shapes."""
+    """With 256 CUs, 65 to 110 rows of the large vocabulary take the 256 x 128
+    tile (one, two and three live 16-row blocks for the waves of the second
+    half, four for the first; 300 rows in tests/test_gpu_lm_hidden_sizes.py
+    leave some none), 129 and 400 rows the 256 x 256 tile, the smaller
+    vocabulary 128 x 128 tiles."""
     say("tiled LM head + statistics", T, hid, V)
     w, wd = weight(V, hid)
     X = synth.hidden_rows(40 + T, T, hid)
