@@ -100,9 +100,9 @@ constexpr bool gemm_groups_fit(int m, int h, int f) {
 }
 
 // Waits out the latency of the last MFMAs before their accumulators are
-// read (32 wait states: the longest 16x16x32 result latency is 16 passes of
-// four cycles, of which the issue of the following instructions covers the
-// rest).
+// read: 32 wait states, where a product of 16 passes (the longest there are;
+// 32x32x16 takes 8, 16x16x32 four) needs 19 between its issue and the first
+// read of its result.
 __device__ __forceinline__ void mfma_drain() {
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 }
@@ -473,7 +473,6 @@ __global__ __launch_bounds__(64 * NW) void lm_head_gemm_kernel(
 // 208 -> 221: every block fetches X).
 // ---------------------------------------------------------------------------
 constexpr int kBigThreads = 256;
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // chunk c of row r lies at position c ^ big_swz(r): any 8 consecutive rows, 8
 // of one parity among 16 and 8 equal mod 4 among 32 fall on distinct positions
@@ -484,29 +483,29 @@ template <int MB, int WR, int XR, bool STATS>
 __global__ __launch_bounds__(kBigThreads, 1) void lm_head_square_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ W, float* __restrict__ logits,
     int T, int hid, int V, int G, float inv_temp, StatPart* __restrict__ part) {
-  constexpr int kBigRows = 64 * MB;                  // rows of W and of X per tile
-  constexpr int kBigSlot = kBigRows * kGemmBK * 2;   // bytes
+  constexpr int kTile = 64 * MB;                     // rows of W and of X per tile
+  constexpr int kSlotBytes = kTile * kGemmBK * 2;   // bytes
   constexpr int LI = 2 * MB;                         // copies per wave and operand a stage
   static_assert((WR == 3 && XR == 2) || (WR == 4 && XR == 4), "the wait counts below");
   // one LDS object per slot (the compiler then knows that reads of one do not
   // wait for copies into another)
-  __shared__ __attribute__((aligned(16))) uint8_t w0[kBigSlot];
-  __shared__ __attribute__((aligned(16))) uint8_t w1[kBigSlot];
-  __shared__ __attribute__((aligned(16))) uint8_t w2[kBigSlot];
-  __shared__ __attribute__((aligned(16))) uint8_t w3[WR > 3 ? kBigSlot : 16];
-  __shared__ __attribute__((aligned(16))) uint8_t x0[kBigSlot];
-  __shared__ __attribute__((aligned(16))) uint8_t x1[kBigSlot];
-  __shared__ __attribute__((aligned(16))) uint8_t x2[XR > 2 ? kBigSlot : 16];
-  __shared__ __attribute__((aligned(16))) uint8_t x3[XR > 2 ? kBigSlot : 16];
+  __shared__ __attribute__((aligned(16))) uint8_t w0[kSlotBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t w1[kSlotBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t w2[kSlotBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t w3[WR > 3 ? kSlotBytes : 16];
+  __shared__ __attribute__((aligned(16))) uint8_t x0[kSlotBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t x1[kSlotBytes];
+  __shared__ __attribute__((aligned(16))) uint8_t x2[XR > 2 ? kSlotBytes : 16];
+  __shared__ __attribute__((aligned(16))) uint8_t x3[XR > 2 ? kSlotBytes : 16];
   uint8_t* const wring[4] = {w0, w1, w2, WR > 3 ? w3 : w2};   // (unused slots take no LDS)
   uint8_t* const xring[4] = {x0, x1, XR > 2 ? x2 : x0, XR > 2 ? x3 : x1};
-  constexpr int kSlices = kBigRows / 64;
+  constexpr int kSlices = kTile / 64;
   const int groups = (G + kSlices - 1) / kSlices;
-  const int passes = (T + kBigRows - 1) / kBigRows;
+  const int passes = (T + kTile - 1) / kTile;
   const int bid = blockIdx.x, r8 = bid >> 3;
   const int pass = r8 % passes, grp = (r8 / passes) * 8 + (bid & 7);
   if (grp >= groups) return;
-  const int j0 = pass * kBigRows;
+  const int j0 = pass * kTile;
   const int r0 = slice_begin(kSlices * grp, G, V);
   const int r1 = slice_begin(kSlices * grp + kSlices, G, V);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -515,7 +514,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_square_kernel(
   const StatPart empty{-INFINITY, 0.f, 0.f, 0x7fffffff};
   if (r0 >= r1) {   // empty block (tiny V): neutral partials only
     if constexpr (STATS)
-      if (tid < kBigRows && j0 + tid < T)
+      if (tid < kTile && j0 + tid < T)
         for (int u = 0; u < kSlices && kSlices * grp + u < G; ++u)
           part[static_cast<size_t>(j0 + tid) * G + kSlices * grp + u] = empty;
     return;
@@ -525,7 +524,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_square_kernel(
   const __amdgpu_buffer_rsrc_t wbuf =
       dma_buffer(W + static_cast<size_t>(r0) * hid, static_cast<uint32_t>(r1 - r0) * hid * 2u);
   const __amdgpu_buffer_rsrc_t xbuf =
-      dma_buffer(X + static_cast<size_t>(j0) * hid, static_cast<uint32_t>(min(kBigRows, T - j0)) * hid * 2u);
+      dma_buffer(X + static_cast<size_t>(j0) * hid, static_cast<uint32_t>(min(kTile, T - j0)) * hid * 2u);
   // copy q of a wave fills rows 8 (LI wave + q) .. + 7 of a slot
   uint32_t voff[LI];
 #pragma unroll
@@ -686,7 +685,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_square_kernel(
     const float it2 = inv_temp * kLog2e;
     // (rows past the block count as -inf: no branches, which spilled)
     __syncthreads();   // every wave is done with the ring
-    StatPart* wpart = reinterpret_cast<StatPart*>(x0);   // [2][kBigRows]
+    StatPart* wpart = reinterpret_cast<StatPart*>(x0);   // [2][kTile]
 #pragma unroll
     for (int ni = 0; ni < MB; ++ni) {
       __builtin_amdgcn_sched_barrier(0);   // one column of blocks at a time
@@ -720,12 +719,12 @@ __global__ __launch_bounds__(kBigThreads, 1) void lm_head_square_kernel(
       }
       p.Z += __shfl_xor(p.Z, 32, 64);
       p.S += __shfl_xor(p.S, 32, 64);
-      if (lh == 0) wpart[wm * kBigRows + wn * 32 * MB + 32 * ni + li] = p;
+      if (lh == 0) wpart[wm * kTile + wn * 32 * MB + 32 * ni + li] = p;
     }
     __syncthreads();
-    if (tid < kBigRows && j0 + tid < T) {
+    if (tid < kTile && j0 + tid < T) {
       StatPart q = wpart[tid];
-      part_merge(q, wpart[kBigRows + tid], inv_temp);
+      part_merge(q, wpart[kTile + tid], inv_temp);
       StatPart* dst = part + static_cast<size_t>(j0 + tid) * G + kSlices * grp;
       dst[0] = q;
 #pragma unroll
@@ -773,7 +772,9 @@ namespace {
 constexpr int kBigRows = 256;
 
 // 256 x 256 tiles: the last pass of 256 rows is more than half full, and the
-// workgroups (one per CU) fill nine tenths of their rounds.
+// workgroups (one per CU) fill nine tenths of their rounds.  The fewest rows
+// that take them, 256 x 128 / 256 x 256: hid 4096, 128256 entries, 129 rows 243
+// / 232 us, 192 264 / 239, 385 490 / 424; hid 5120, 50257, 129 158 / 129.
 bool big_tiles(int T, int G, int cus) {
   if (T <= kGemmMinRows || (T - 1) % kBigRows < kBigRows / 2) return false;
   const long long wg = static_cast<long long>(G / 4) * ((T + kBigRows - 1) / kBigRows);
