@@ -29,7 +29,10 @@
 //     others take a 32-bit window cut from the node's ancestor bitmask.
 //     Online softmax in fp32, base 2, with a lazily raised running max (the
 //     accumulators are rescaled only when a block's max passes the reference
-//     by more than 2^8).
+//     by more than 2^8).  A weight equal to the reference is exact in bf16, so
+//     fewer references cost trees of one tile a little: error against 64 bits
+//     3.27e-3 where four waves with a reference each had 3.13e-3; raising it at
+//     every block gives 3.17e-3 and takes 3 - 10 % longer.
 //  2. merge: combines the splits' partials: (max, sum) in fp32 and the
 //     output normalised by its sum, in bf16 (half the bytes of fp32; a
 //     normalised partial stays within the range of the values).
@@ -393,28 +396,31 @@ __device__ __forceinline__ SeqPlan resolve_batch(const BatchArgs& p, int x, int 
 // or (MERGE) merge grid.  A device-planned batch's grid is as long as any plan
 // of sequences whose rows are their own; where row ranges overlap (the entries
 // are the device's) the plan can be longer, and a workgroup takes every
-// gridDim.x-th index.  (The first index outside the loop: one loop over all of
-// them took 102.1 us for eight GQA sequences, this form 100.0, and the first
-// index alone, which left such sequences out, 99.3.)
+// gridDim.x-th index.  The attend kernel takes its first index outside the
+// loop: one loop over all of them took 102.1 us for eight GQA sequences, this
+// form 100.0, and the first index alone, which left such sequences out, 99.3.
+// (The merge is faster in one loop, by 1.9 us.)  What follows from the thread's
+// number must not be kept from one index for the next, in registers that spilled
+// (84): it is taken anew each time.
 template <bool DEVB, bool MERGE, typename F>
 __device__ __forceinline__ void for_items(const BatchArgs& p, F work) {
-  int x = static_cast<int>(blockIdx.x);
+  int x = static_cast<int>(blockIdx.x), tid = static_cast<int>(threadIdx.x);
   if constexpr (DEVB) {
-    int tid = static_cast<int>(threadIdx.x), total;
-    const SeqPlan first = resolve_batch<MERGE>(p, x, tid, total);
-    if (first.T == 0) return;
-    work(first, x, tid);
-    for (x += static_cast<int>(gridDim.x); x < total; x += static_cast<int>(gridDim.x)) {
-      __syncthreads();   // the LDS of one index is read out
-      // (the thread's number anew each time: what follows from it would
-      // otherwise be kept for the next round, in registers that spilled)
+    int total = x + 1;
+    if constexpr (!MERGE) {
+      const SeqPlan first = resolve_batch<MERGE>(p, x, tid, total);
+      if (first.T == 0) return;
+      work(first, x, tid);
+      x += static_cast<int>(gridDim.x);
+    }
+    for (; x < total; x += static_cast<int>(gridDim.x)) {
+      if constexpr (!MERGE) __syncthreads();   // the LDS of one index is read out
       asm volatile("" : "+v"(tid));
       const SeqPlan sq = resolve_batch<MERGE>(p, x, tid, total);
       work(sq, x, tid);
     }
   } else {
-    work(resolve(p, seq_of(p, x, [](const SeqPlan& q) { return MERGE ? q.merge0 : q.item0; })), x,
-         static_cast<int>(threadIdx.x));
+    work(resolve(p, seq_of(p, x, [](const SeqPlan& q) { return MERGE ? q.merge0 : q.item0; })), x, tid);
   }
 }
 
