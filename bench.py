@@ -1023,8 +1023,8 @@ def lm_head_traffic(Ts, on_gpu=False):
             # 2); an unpaired launch of the entry points must not stand in
             if key in per and len(targs) > 4 and targs[4] != "2":
                 continue
-        elif kernel == "lm_head_gemm_kernel" and targs[-1] == "true":   # <BM, BN, NW, NST, STATS>
-            key = (kernel, 0)
+        elif kernel in ("lm_head_gemm_kernel", "lm_head_square_kernel") and targs[-1] == "true":
+            key = ("tiled", 0)   # <BM, BN, NW, NST, STATS> or <MB, WR, XR, STATS>
         elif kernel in ("lm_head_dyn_small_kernel", "lm_head_dyn_large_kernel"):
             key = (kernel, 0)
         else:
@@ -1038,8 +1038,8 @@ def lm_head_traffic(Ts, on_gpu=False):
             key = ("lm_head_pair_kernel", 1 if T <= 16 else 2)
         elif T <= 64:
             key = ("lm_head_hyb_kernel", 4)
-        else:   # the tiled kernel where it takes the launch, else the 128-node streaming tile
-            key = ("lm_head_gemm_kernel", 0) if ("lm_head_gemm_kernel", 0) in per else ("lm_head_hyb_kernel", 8)
+        else:   # the tiled kernels where they take the launch, else the 128-node streaming tile
+            key = ("tiled", 0) if ("tiled", 0) in per else ("lm_head_hyb_kernel", 8)
         if key not in per:
             return None
         tot += per[key]
